@@ -1,0 +1,42 @@
+"""Edges of the kernels' tiles and of the rules that choose them, against the
+oracle or against the general form of the same kernel."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+import paper_2111_11788_amd as mm
+from oracle import field, rng
+from workloads import Workload
+
+
+def _wl(**kw):
+    base = dict(name="k", n0=8, levels=1, sigma2=1.0, corr_len=0.3, n_modes=20, qoi=0, rtol=1e-12, max_iter=3000,
+                solver=0, precision=0, batch=16)
+    base.update(kw)
+    return Workload(**base)
+
+
+# meshes below 64^3: 4 samples to a workgroup at 4^3 and 8^3, one at 16^3, a
+# quarter of one at 32^3; counts on both sides of that, K1 <= 8, 16 and 32, and
+# mode counts at which the workgroup's coefficients no longer fit (the row-wise form)
+@pytest.mark.parametrize("n,M,corr,count", [(4, 8, 0.5, 1), (4, 20, 0.2, 5), (4, 512, 0.1, 4), (8, 3, 0.5, 4),
+                                            (8, 128, 0.2, 9), (8, 1, 0.3, 1), (8, 300, 0.2, 13), (16, 20, 0.1, 1),
+                                            (16, 512, 0.2, 3), (16, 1500, 0.2, 2), (32, 64, 0.5, 1), (32, 512, 0.1, 3),
+                                            (32, 700, 0.2, 2), (8, 2000, 0.1, 5)])
+def test_field_below_64_matches_oracle(n, M, corr, count):
+    # tolerance: the sums differ in order only; exp turns an absolute error of
+    # a few 1e-15 times |g| <= ~10 into a relative one
+    wl = _wl(n0=n, n_modes=M, corr_len=corr)
+    ctx = mm.Context(wl, arena_bytes=64 << 20)
+    xi = ctx.draw_xi(0, 7, count)
+    k, k32 = ctx.field(n, xi, want32=True)
+    want = field.kappa(n, corr, 1.0, M, rng.draw_xi(wl.seed, 0, 7, count, M))
+    got = k.cpu().numpy()
+    assert np.max(np.abs(got - want) / want) < 1e-13
+    assert np.array_equal(k32.cpu().numpy(), got.astype(np.float32))
+    # a sample's field does not depend on its batch
+    assert torch.equal(ctx.field(n, xi[count - 1:])[0], k[count - 1])
+    ctx.close()
