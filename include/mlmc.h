@@ -442,7 +442,8 @@ enum {
   MLMC_FUSE_PRESMOOTH = 16, /* Chebyshev degree 1 with the LDS engine (zvar bit 2) and PROLONG and
                               RESTRICT on: the zero-start pre-smoothing step c D^-1 b of each V-cycle
                               level is formed inside the residual and the correction steps, never
-                              stored (supersedes UPDATE on those levels) */
+                              stored (supersedes UPDATE on those levels); from degree 2 on, with the
+                              LDS engine, it is formed inside the second smoothing step instead */
   MLMC_FUSE_DIRECTION = 32, /* LDS engine: the PCG direction p = z + beta p is formed inside the operator
                               apply q = A p, which also applies the previous step's x += alpha p (two
                               direction buffers); the last x update of a solve runs after it */

@@ -127,6 +127,14 @@ hipError_t launch_cheb_prolong_presmoothed(int n, int B, const T* kap, const T* 
                                            const int* active, hipStream_t st, SolveState* dot = nullptr,
                                            uint32_t* nparts = nullptr, const T* b1 = nullptr,
                                            const int* bstate = nullptr);
+// The second smoothing step from a zero iterate with the first formed on the
+// fly: out = x + c1 x + c2 D^-1 (b - A x), x = c20 D^-1 b; save (may be null)
+// receives x.  Usable when presmooth_step_usable(n, B).
+template <class T>
+hipError_t launch_cheb_presmoothed(int n, int B, const T* kap, const T* b, T* out, T* save, double c20, double c1,
+                                   double c2, const int* active, hipStream_t st);
+template <class T>
+bool presmooth_step_usable(int n, int B);
 // The pre-smoothed residual restriction with the PCG residual update of the
 // previous iteration fused in: r = r_old - alpha q (r_old in r0 or r1 by
 // s.pstate bit 3; not on a first iteration, s.pstate bit 1) formed on the fly,

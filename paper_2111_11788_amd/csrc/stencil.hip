@@ -2031,6 +2031,23 @@ hipError_t launch_cheb_prolong_presmoothed(int n, int B, const T* kap, const T* 
 }
 
 template <class T>
+bool presmooth_step_usable(int n, int B) {
+  return n >= 4 && !use_small<T>(n) && zlds_ok<T, OP_Z1>(zgeom<T>(n, B));
+}
+
+template <class T>
+hipError_t launch_cheb_presmoothed(int n, int B, const T* kap, const T* b, T* out, T* save, double c20, double c1,
+                                   double c2, const int* active, hipStream_t st) {
+  constexpr int V = ZV<T>::V;
+  if (!presmooth_step_usable<T>(n, B)) return hipErrorInvalidValue;
+  OpArgs<T> op;
+  op.c2 = T(c20);
+  return zlaunch_lds<T, true, false, OP_Z1>(n, B, b, nullptr, kap, active, nullptr, 0,
+                                            EpiCheb<T, V, false, false>{b, nullptr, out, T(c1), T(c2), save}, nullptr,
+                                            st, op);
+}
+
+template <class T>
 hipError_t launch_pcg_update_zero(int n, int B, const T* kap, T* x, const T* p, T* r, const T* q, T* z, double c2,
                                   SolveState s, uint32_t* nparts, hipStream_t st, int var) {
   if (use_small<T>(n)) return hipErrorInvalidValue;
@@ -2241,6 +2258,9 @@ hipError_t launch_convert(size_t count, const Ts* src, Td* dst, hipStream_t st) 
   template hipError_t launch_residual_restrict<T>(int, int, const T*, const T*, const T*, T*, const int*, \
                                                   hipStream_t, bool, double);                          \
   template bool presmooth_usable<T>(int, int);                                                         \
+  template bool presmooth_step_usable<T>(int, int);                                                    \
+  template hipError_t launch_cheb_presmoothed<T>(int, int, const T*, const T*, T*, T*, double, double, double, \
+                                                 const int*, hipStream_t);                              \
   template bool dir_usable<T>(int, int);                                                               \
   template hipError_t launch_pcg_dir_apply<T>(int, int, const T*, const T*, T*, T*, T*, T*, const int*,  \
                                               SolveState, uint32_t*, hipStream_t);                     \

@@ -40,3 +40,22 @@ def test_field_below_64_matches_oracle(n, M, corr, count):
     # a sample's field does not depend on its batch
     assert torch.equal(ctx.field(n, xi[count - 1:])[0], k[count - 1])
     ctx.close()
+
+
+@pytest.mark.parametrize("n,deg", [(4, 2), (8, 3), (16, 2), (32, 2), (32, 4), (64, 2), (128, 2)])
+@pytest.mark.parametrize("prec", [0, 1])
+def test_zero_step_inside_the_second_step_gives_the_stored_bits(n, deg, prec):
+    # Chebyshev degree >= 2: the zero-start smoothing step formed inside the
+    # second one, against the step stored by its own kernel
+    ctx = mm.Context(_wl(n0=n), cheb_degree=deg, arena_bytes=1 << 30)
+    dt = torch.float64 if prec == 0 else torch.float32
+    g = torch.Generator(device="cuda").manual_seed(n + deg)
+    kap = torch.exp(torch.randn((2, n ** 3), generator=g, dtype=torch.float64, device="cuda")).to(dt)
+    r = mm.to_grid(torch.randn((2, (n - 1) ** 3), generator=g, dtype=torch.float64, device="cuda").to(dt), n)
+    f = ctx.vcycle if prec == 0 else ctx.vcycle_f32
+    out = []
+    for fuse in (mm.FUSE_PROLONG | mm.FUSE_RESTRICT | mm.FUSE_PRESMOOTH, mm.FUSE_PROLONG | mm.FUSE_RESTRICT):
+        ctx.set_tuning(fuse=fuse, vsmall_fp32=0, vsmall_fp64=0)
+        out.append(f(n, kap, r))
+    assert bool(torch.isfinite(out[0]).all()) and torch.equal(out[0], out[1])
+    ctx.close()
