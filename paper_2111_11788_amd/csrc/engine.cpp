@@ -516,6 +516,9 @@ int solve_impl(mlmc_ctx* ctx, SolveWork& w, const double* kap, double* u, int32_
   if (w.precision == MLMC_PREC_FP64) {
     auto& L = w.L64;
     L[0].kap = const_cast<double*>(kap);
+    if (w.exec_kap != kap || w.exec_u != u) w.release_graphs();
+    w.exec_kap = kap;
+    w.exec_u = u;
     for (size_t l = 1; l < L.size(); ++l)
       LAUNCH(MLMC_K_COARSEN, (elems(L[l - 1].n) + elems(L[l].n)) * B * 8,
              launch_coarsen<double>(L[l - 1].n, B, L[l - 1].kap, L[l].kap, st));

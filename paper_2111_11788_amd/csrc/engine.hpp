@@ -121,6 +121,10 @@ struct SolveWork {
   StateBufs outer, inner;
   // captured PCG iteration per precision (0: fp64, 1: fp32); tied to the buffers above
   hipGraphExec_t iter_exec[2] = {nullptr, nullptr};
+  // the caller's kappa and solution the fp64 iteration was captured with (a
+  // step-level solve may come with others: the iteration is captured again)
+  const double* exec_kap = nullptr;
+  const double* exec_u = nullptr;
 
   void release_graphs() {
     for (auto& g : iter_exec)

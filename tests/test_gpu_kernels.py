@@ -59,3 +59,19 @@ def test_zero_step_inside_the_second_step_gives_the_stored_bits(n, deg, prec):
         out.append(f(n, kap, r))
     assert bool(torch.isfinite(out[0]).all()) and torch.equal(out[0], out[1])
     ctx.close()
+
+
+@pytest.mark.parametrize("solver", [0, 1])
+def test_fp64_solves_on_other_arrays(solver):
+    # one context, one batch size, different kappa and solution arrays: the
+    # captured iteration is taken again for them
+    n = 8
+    ctx = mm.Context(_wl(n0=n, solver=solver, rtol=1e-9), arena_bytes=64 << 20)
+    kap = ctx.field(n, ctx.draw_xi(0, 0, 6))
+    keep = [ctx.solve(n, kap[k:k + 1].contiguous()) for k in (0, 3, 5, 0)]
+    for k, (u, it) in zip((0, 3, 5, 0), keep):
+        one = mm.Context(_wl(n0=n, solver=solver, rtol=1e-9), arena_bytes=64 << 20)
+        w, iw = one.solve(n, kap[k:k + 1].contiguous())
+        assert torch.equal(u, w) and it[0] == iw[0]
+        one.close()
+    ctx.close()
