@@ -155,8 +155,10 @@ struct SolveWork {
           L64[l].b = cv.take<double>(B * S);
         }
         L64[l].x = cv.take<double>(B * S);
-        L64[l].xo = cv.take<double>(B * S);
-        if (nl > 1 || l > 0) L64[l].t = cv.take<double>(B * S);
+        if (nl > 1 && nn > 2) {   // smoothed levels: not the one unknown of 2^3, not a lone (Jacobi) level
+          L64[l].xo = cv.take<double>(B * S);
+          L64[l].t = cv.take<double>(B * S);
+        }
       }
     } else {
       inner.carve(cv, B, n);
@@ -176,8 +178,10 @@ struct SolveWork {
         L32[l].kap = cv.take<float>(B * elem_count(nn));
         if (l > 0) L32[l].b = cv.take<float>(B * S);
         L32[l].x = cv.take<float>(B * S);
-        L32[l].xo = cv.take<float>(B * S);
-        if (nl > 1 || l > 0) L32[l].t = cv.take<float>(B * S);
+        if (nl > 1 && nn > 2) {
+          L32[l].xo = cv.take<float>(B * S);
+          L32[l].t = cv.take<float>(B * S);
+        }
       }
     }
   }

@@ -15,7 +15,10 @@ struct ZV { static constexpr int V = 16 / (int)sizeof(T); };
 // Geometry of a z-marching launch on an n^3 grid for B samples.
 // A thread owns V consecutive nodes i0 .. i0+V-1 of row j and marches over a
 // chunk of planes; a workgroup holds `rows` rows of one sample and one plane
-// chunk.  Workgroups of a sample are numbered rb + row_blocks * zb.
+// chunk.  Workgroups of a sample are numbered rb + row_blocks * zb.  Partial
+// sums are taken per row block and unit of `zu` planes (planes 1 + u zu ..
+// (u + 1) zu; a chunk is a whole number of units), numbered rb + row_blocks *
+// u, so up to 64^3 they do not depend on how the planes are split.
 struct ZGeom {
   int n = 0;
   int G = 0;            // vector groups per row (n / V)
@@ -23,12 +26,45 @@ struct ZGeom {
   int row_blocks = 0;   // workgroups per plane chunk
   int zc = 1;           // plane chunks
   int zlen = 0;         // planes per chunk
+  int zu = 1;           // planes per partial sum
   int threads = 256;    // threads per workgroup
-  __host__ __device__ uint32_t parts() const { return (uint32_t)row_blocks * zc; }
+  __host__ __device__ uint32_t blocks() const { return (uint32_t)row_blocks * zc; }
+  __host__ __device__ uint32_t parts() const { return (uint32_t)row_blocks * ((n - 1 + zu - 1) / zu); }
 };
 
 // waves of a launch from which the samples' planes are no longer split
 constexpr long kFillWaves = 8192;
+// the same for meshes up to 64^3, whose planes split down to a unit: four waves
+// per SIMD (2048 and 8192 measured 2.93 and 2.63 ms against 2.42 on a burst of
+// 400 served requests, 39.4 and 40.2 ms against 39.4 on 1024 samples of 64^3)
+constexpr long kSplitWaves = 4096;
+
+// The planes of a launch of `waves` waves in one chunk, split over workgroups
+// while the launch does not fill the chip.
+inline void zsplit(ZGeom& g, long waves) {
+  const int n = g.n;
+  if (n <= 64) {
+    // down to one unit: a workgroup's planes are a serial chain of about a
+    // microsecond each, and the two planes a chunk stages beyond its own are
+    // cheap while the chip is not full (32 pairs of 32^3 / 16^3, mixed: 1.92 ->
+    // 1.31 ms with chunks of 4 planes in place of 16; a 64^3 level of three
+    // 128^3 samples likewise)
+    g.zu = n == 64 ? 8 : 4;
+    g.zlen = (n - 1 + g.zu - 1) / g.zu * g.zu;
+    g.zc = 1;
+    while (waves * g.zc < kSplitWaves && g.zlen % (2 * g.zu) == 0) {
+      g.zlen /= 2;
+      g.zc = (n - 1 + g.zlen - 1) / g.zlen;
+    }
+    return;
+  }
+  // larger meshes: one partial sum per chunk, chunks of at least 8 planes
+  int zc = 1;
+  while (waves * zc < kFillWaves && (n - 1) / (zc * 2) >= 8) zc *= 2;
+  g.zc = zc;
+  g.zlen = (n - 1 + zc - 1) / zc;
+  g.zu = g.zlen;
+}
 
 template <class T>
 inline ZGeom zgeom(int n, int B) {
@@ -47,12 +83,7 @@ inline ZGeom zgeom(int n, int B) {
   g.rows = g.threads / g.G;
   if (g.rows < 1) g.rows = 1;
   g.row_blocks = (n - 1 + g.rows - 1) / g.rows;
-  // split the planes when there are few samples, so the chip has >= ~8 waves per SIMD
-  const long waves = (long)B * g.row_blocks * (g.threads / 64);
-  int zc = 1;
-  while (waves * zc < kFillWaves && (n - 1) / (zc * 2) >= 8) zc *= 2;
-  g.zc = zc;
-  g.zlen = (n - 1 + zc - 1) / zc;
+  zsplit(g, (long)B * g.row_blocks * (g.threads / 64));
   return g;
 }
 
@@ -64,11 +95,7 @@ inline ZGeom zgeom_rows(int n, int B, int rows) {
   if (g.G < 1 || rows < 1) return g;
   g.rows = rows;
   g.row_blocks = (n - 1 + rows - 1) / rows;
-  const long waves = (long)B * g.row_blocks * (g.threads / 64);
-  int zc = 1;
-  while (waves * zc < kFillWaves && (n - 1) / (zc * 2) >= 8) zc *= 2;
-  g.zc = zc;
-  g.zlen = (n - 1 + zc - 1) / zc;
+  zsplit(g, (long)B * g.row_blocks * (g.threads / 64));
   return g;
 }
 

@@ -36,16 +36,51 @@ namespace {
 
 __device__ __forceinline__ int ilog2(int n) { return 31 - __clz(n); }
 
-__device__ __forceinline__ double block_sum(double v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
+// One DPP move of a double (both halves), 0 where the source lane or row is masked off
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_move(double x) {
+  const long long v = __double_as_longlong(x);
+  const int lo = __builtin_amdgcn_update_dpp(0, (int)(v & 0xffffffffll), CTRL, ROWS, 0xF, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, (int)(v >> 32), CTRL, ROWS, 0xF, false);
+  return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+
+// The sum over the 64 lanes of a wave (all of them active), in lane 63: row
+// shifts within the 16-lane rows, then the rows' sums broadcast upwards
+__device__ __forceinline__ double wave_sum63(double v) {
+  v += dpp_move<0x111, 0xF>(v);   // row_shr:1
+  v += dpp_move<0x112, 0xF>(v);   // row_shr:2
+  v += dpp_move<0x114, 0xF>(v);   // row_shr:4
+  v += dpp_move<0x118, 0xF>(v);   // row_shr:8
+  v += dpp_move<0x142, 0xA>(v);   // row_bcast:15 into rows 1 and 3
+  v += dpp_move<0x143, 0xC>(v);   // row_bcast:31 into rows 2 and 3
+  return v;
+}
+
+// out = the workgroup's sum of v, taken by every thread of it (waves in
+// order).  Two calls need a barrier between them beyond the one in here.
+__device__ __forceinline__ void unit_sum(double v, double* out) {
   __shared__ double wsum[kBlock / 64];
+  v = wave_sum63(v);
+  if ((threadIdx.x & 63) == 63) wsum[threadIdx.x >> 6] = v;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    double t = 0.0;
+    const int nw = blockDim.x >> 6;
+    for (int w = 0; w < nw; ++w) t += wsum[w];
+    *out = t;
+  }
+}
+
+__device__ __forceinline__ double block_sum(double v) {
+  __shared__ double bsum[kBlock / 64];
+  v = wave_sum63(v);
   const int nw = blockDim.x >> 6;
-  if ((threadIdx.x & 63) == 0) wsum[threadIdx.x >> 6] = v;
+  if ((threadIdx.x & 63) == 63) bsum[threadIdx.x >> 6] = v;
   __syncthreads();
   double t = 0.0;
   if (threadIdx.x == 0)
-    for (int w = 0; w < nw; ++w) t += wsum[w];
+    for (int w = 0; w < nw; ++w) t += bsum[w];
   return t;
 }
 
@@ -578,7 +613,7 @@ struct EpiDirApply {
       // a fresh iterate is written, not updated (it holds no value yet)
       T xn[V];
 #pragma unroll
-      for (int v = 0; v < V; ++v) xn[v] = fresh ? a * pv[v] : xv[v] + a * pv[v];
+      for (int v = 0; v < V; ++v) xn[v] = fresh ? a * pv[v] : fma(a, pv[v], xv[v]);
       vstore<T, V>(x + pos, xn);
     }
   }
@@ -604,7 +639,7 @@ __global__ void __launch_bounds__(256) k_zmarch(ZGeom g, size_t stride, T h, con
                                                 const float* __restrict__ dadd) {
   static_assert(!(PRO && (PF || !NEED_U)), "the fused prolongation uses the plain u window");
   static_assert(!(ADDD && (PF || PRO || !NEED_U)), "the added vector uses the plain u window");
-  const uint32_t per = g.parts();
+  const uint32_t per = g.blocks();
   const uint32_t lin = xcd_remap(blockIdx.x, gridDim.x);
   const uint32_t b = lin / per;
   const uint32_t part = lin - b * per;
@@ -612,15 +647,16 @@ __global__ void __launch_bounds__(256) k_zmarch(ZGeom g, size_t stride, T h, con
   const int rb = (int)(part % (uint32_t)g.row_blocks), zb = (int)(part / (uint32_t)g.row_blocks);
   const int n = g.n, n2 = n * n;
   const int gx = (int)threadIdx.x % g.G, jr = (int)threadIdx.x / g.G;
-  const int j = 1 + rb * g.rows + jr;
+  const int jt = 1 + rb * g.rows + jr;
+  const bool valid = jr < g.rows && jt <= g.n - 1;
+  const int j = jt <= g.n - 1 ? jt : g.n - 1;   // threads beyond the tile follow its last row, without output
   const int i0 = gx * V;
   const int k0 = 1 + zb * g.zlen;
   int k1 = k0 + g.zlen;
   if (k1 > n) k1 = n;
-  const bool valid = jr < g.rows && j <= n - 1 && k0 < k1;
   double acc = 0.0;
   if constexpr (Epi::kBegin) epi.begin(b);
-  if (valid) {
+  if (k0 < k1) {   // uniform over the workgroup
     const T* ub = u ? u + (size_t)b * stride : nullptr;
     const float* db = ADDD ? dadd + (size_t)b * stride : nullptr;
     const T* kb = kap + (size_t)b * n2 * n;
@@ -796,7 +832,12 @@ __global__ void __launch_bounds__(256) k_zmarch(ZGeom g, size_t stride, T h, con
         au[v] = h * (ks * uc[v] * third - far * twelfth);
         dg[v] = h * ks * third;
       }
-      epi((size_t)b * stride + i0 + (size_t)n * j + (size_t)n2 * k, au, dg, uc, ok, acc);
+      if (valid) epi((size_t)b * stride + i0 + (size_t)n * j + (size_t)n2 * k, au, dg, uc, ok, acc);
+      if (Epi::kReduce && (k % g.zu == 0 || k == k1 - 1)) {   // the last plane of a unit
+        unit_sum(acc, partial + (size_t)b * pstride + (size_t)((k - 1) / g.zu) * g.row_blocks + rb);
+        acc = 0.0;
+        __syncthreads();
+      }
       if (NEED_U) {
 #pragma unroll
         for (int r = 0; r < 3; ++r)
@@ -811,10 +852,6 @@ __global__ void __launch_bounds__(256) k_zmarch(ZGeom g, size_t stride, T h, con
 #pragma unroll
         for (int c = 0; c < V + 1; ++c) K[0][r][c] = K[1][r][c];
     }
-  }
-  if (Epi::kReduce) {
-    acc = block_sum(acc);
-    if (threadIdx.x == 0) partial[(size_t)b * pstride + part] = acc;
   }
 }
 
@@ -948,7 +985,7 @@ __global__ void __launch_bounds__(256) k_zlds(ZGeom g, size_t stride, T h, const
   typedef typename Vec<float, V>::type fvt;
   typedef typename Vec<T, V>::type vt;
   extern __shared__ __align__(16) unsigned char zsmem[];
-  const uint32_t per = g.parts();
+  const uint32_t per = g.blocks();
   const uint32_t lin = xcd_remap(blockIdx.x, gridDim.x);
   const uint32_t b = lin / per;
   const uint32_t part = lin - b * per;
@@ -1128,11 +1165,19 @@ __global__ void __launch_bounds__(256) k_zlds(ZGeom g, size_t stride, T h, const
         if (ADDD) {
           // the completed correction in fp32, as the separate update would store it
           fvt dd = pd[ADDD ? m : 0];
-          if (d_owe) dd = d_read ? dd + d_a * pq[ADDD ? m : 0] : d_a * pq[ADDD ? m : 0];
+          if (d_owe) {
+#pragma unroll
+            for (int t = 0; t < V; ++t)
+              dd[t] = d_read ? fma(d_a, pq[ADDD ? m : 0][t], dd[t]) : d_a * pq[ADDD ? m : 0][t];
+          }
 #pragma unroll
           for (int t = 0; t < V; ++t) pu[m][t] += (T)dd[t];
         }
-        if (DIR && dir_prev) pu[m] = pu[m] + dbeta * pp[DIR ? m : 0];
+        // explicit fused multiply-adds: every copy of this code rounds the same,
+        // so a value does not depend on where a chunk of planes starts
+        if (DIR && dir_prev)
+#pragma unroll
+          for (int t = 0; t < V; ++t) pu[m][t] = fma(dbeta, pp[DIR ? m : 0][t], pu[m][t]);
       }
     }
   };
@@ -1253,6 +1298,11 @@ __global__ void __launch_bounds__(256) k_zlds(ZGeom g, size_t stride, T h, const
         }
         epi(pos0 + (size_t)n2 * (k - k0), au, dg, uc, ok, acc);
       }
+      // the last plane of a unit (the next sum is a plane's barriers away)
+      if (Epi::kReduce && (k % g.zu == 0 || k == k1 - 1)) {
+        unit_sum(acc, partial + (size_t)b * pstride + (size_t)((k - 1) / g.zu) * g.row_blocks + rb);
+        acc = 0.0;
+      }
       if (k + 1 < k1) {
         // u plane k+2 (OP_Z1: from kappa planes k+1, k+2, stored in earlier
         // steps; kappa plane k+3 takes the slot of plane k-1 below)
@@ -1277,10 +1327,6 @@ __global__ void __launch_bounds__(256) k_zlds(ZGeom g, size_t stride, T h, const
         const int t = sm; sm = s0; s0 = sp; sp = t;
       }
     }
-  }
-  if (Epi::kReduce) {
-    acc = block_sum(acc);
-    if (threadIdx.x == 0) partial[(size_t)b * pstride + part] = acc;
   }
 }
 
@@ -1355,7 +1401,7 @@ __global__ void __launch_bounds__(256, (resr_min_waves<T, V, Z1, UPD>())) k_resr
   typedef typename Vec<T, V>::type vt;
   constexpr int KOFF = Z1 ? 1 : 0, KP = Z1 ? 4 : 2, LEAD = Z1 ? 3 : 1;
   extern __shared__ __align__(16) unsigned char zsmem[];
-  const uint32_t per = g.parts();
+  const uint32_t per = g.blocks();
   const uint32_t lin = xcd_remap(blockIdx.x, gridDim.x);
   const uint32_t b = lin / per;
   const uint32_t part = lin - b * per;
@@ -1586,6 +1632,12 @@ __global__ void __launch_bounds__(256, (resr_min_waves<T, V, Z1, UPD>())) k_resr
         }
       }
       if (kk + 1 <= kt1) prep_u(kk + 2);   // kappa planes kk+1, kk+2 are in the ring
+      if constexpr (UPD) {
+        if (kk < k1 && (kk % g.zu == 0 || kk == k1 - 1)) {   // the last plane of a unit
+          unit_sum(racc, upd.partial + (size_t)b * upd.pstride + (size_t)((kk - 1) / g.zu) * g.row_blocks + rb);
+          racc = 0.0;
+        }
+      }
       __syncthreads();
       // in-plane full weighting of t at the owned coarse node, folded over planes
       if (owner) {
@@ -1628,10 +1680,6 @@ __global__ void __launch_bounds__(256, (resr_min_waves<T, V, Z1, UPD>())) k_resr
       const int tu = sm; sm = s0; s0 = sp; sp = tu;
     }
   }
-  if constexpr (UPD) {
-    racc = block_sum(racc);
-    if (threadIdx.x == 0) upd.partial[(size_t)b * upd.pstride + part] = racc;
-  }
 }
 
 // the corrected smoothing step with its operand formed on the fly stages two
@@ -1646,7 +1694,7 @@ hipError_t zlaunch_lds(int n, int B, const T* u, const T* xc, const T* kap, cons
   const ZGeom g = zlds_geom<T, PRO, OP>(n, B);
   if (!zlds_ok<T, OP, PRO>(g)) return hipErrorInvalidValue;
   if (nparts) *nparts = g.parts();
-  const uint32_t blocks = g.parts() * (uint32_t)B;
+  const uint32_t blocks = g.blocks() * (uint32_t)B;
   const size_t lds = zlds_bytes<T, OP, PRO>(g);
   const size_t cs = PRO ? grid_stride(n / 2) : 0;
   switch (halo_mode(g.G)) {
@@ -1689,7 +1737,7 @@ hipError_t zlaunch(int n, int B, const T* u, const T* kap, const int* active, do
   const ZGeom g = zgeom<T>(n, B);
   if (g.G < 1) return hipErrorInvalidValue;
   if (nparts) *nparts = g.parts();
-  const uint32_t blocks = g.parts() * (uint32_t)B;
+  const uint32_t blocks = g.blocks() * (uint32_t)B;
   if (var & ZVAR_PREFETCH)
     k_zmarch<T, V, NEED_U, true, false, false, Epi><<<dim3(blocks), dim3(g.threads), 0, st>>>(
         g, grid_stride(n), T(1) / T(n), u, kap, active, partial, pstride, epi, nullptr, 0, nullptr);
@@ -1713,7 +1761,7 @@ hipError_t zlaunch_addd(int n, int B, const T* u, const float* d, const T* kap, 
   const ZGeom g = zgeom<T>(n, B);
   if (g.G < 1) return hipErrorInvalidValue;
   if (nparts) *nparts = g.parts();
-  const uint32_t blocks = g.parts() * (uint32_t)B;
+  const uint32_t blocks = g.blocks() * (uint32_t)B;
   k_zmarch<T, V, true, false, false, true, Epi><<<dim3(blocks), dim3(g.threads), 0, st>>>(
       g, grid_stride(n), T(1) / T(n), u, kap, active, partial, pstride, epi, nullptr, 0, d);
   return hipGetLastError();
@@ -1729,7 +1777,7 @@ hipError_t zlaunch_pro(int n, int B, const T* u, const T* xc, const T* kap, cons
   const ZGeom g = zgeom<T>(n, B);
   if (g.G < 1) return hipErrorInvalidValue;
   if (nparts) *nparts = g.parts();
-  const uint32_t blocks = g.parts() * (uint32_t)B;
+  const uint32_t blocks = g.blocks() * (uint32_t)B;
   k_zmarch<T, V, true, false, true, false, Epi><<<dim3(blocks), dim3(g.threads), 0, st>>>(
       g, grid_stride(n), T(1) / T(n), u, kap, active, partial, pstride, epi, xc, grid_stride(n / 2), nullptr);
   return hipGetLastError();
@@ -2167,7 +2215,7 @@ hipError_t launch_residual_restrict(int n, int B, const T* kap, const T* b, cons
                                    hipStream_t st, bool presmooth, double c2) {
   constexpr int V = ZV<T>::V;
   const ZGeom g = resr_geom<T>(n, B);
-  const uint32_t blocks = g.parts() * (uint32_t)B;
+  const uint32_t blocks = g.blocks() * (uint32_t)B;
   if (presmooth) {
     if (!presmooth_usable<T>(n, B)) return hipErrorInvalidValue;
     resr_dispatch<T, V, true, false>(g, blocks, resr_bytes<T, true>(g), st, grid_stride(n), T(1) / T(n), nullptr, b,
@@ -2194,7 +2242,7 @@ hipError_t launch_residual_restrict_update(int n, int B, const T* kap, const T* 
   u.alpha = s.alpha;
   u.partial = s.partial;
   u.pstride = s.pstride;
-  const uint32_t blocks = g.parts() * (uint32_t)B;
+  const uint32_t blocks = g.blocks() * (uint32_t)B;
   resr_dispatch<T, V, true, true>(g, blocks, resr_bytes<T, true>(g), st, grid_stride(n), T(1) / T(n), nullptr, r0, kap,
                                   s.active, bc, grid_stride(n / 2), T(c2), u);
   return hipGetLastError();

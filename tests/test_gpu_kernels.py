@@ -75,3 +75,21 @@ def test_fp64_solves_on_other_arrays(solver):
         assert torch.equal(u, w) and it[0] == iw[0]
         one.close()
     ctx.close()
+
+
+# the planes of a small launch are split over workgroups (32^3: chunks of 4
+# planes for one sample, one chunk for 1100), a sample's sums are not: the same
+# sample alone and in a batch that fills the chip has the same bits
+@pytest.mark.parametrize("n,B,prec,deg", [(8, 70, 0, 1), (16, 700, 0, 2), (16, 700, 1, 1), (32, 1100, 1, 2),
+                                          (32, 600, 0, 1), (64, 300, 1, 1), (64, 130, 0, 2)])
+def test_split_planes_leave_a_samples_bits(n, B, prec, deg):
+    ctx = mm.Context(_wl(n0=n, precision=prec, rtol=1e-9), cheb_degree=deg, arena_bytes=12 << 30)
+    xi = ctx.draw_xi(0, 0, B)
+    kap = ctx.field(n, xi)
+    u, it = ctx.solve(n, kap)
+    for k in (0, B - 1):
+        u1, it1 = ctx.solve(n, kap[k:k + 1].contiguous())
+        assert torch.equal(u1[0], u[k]) and it1[0] == it[k]
+    u3, it3 = ctx.solve(n, kap[1:4].contiguous())
+    assert torch.equal(u3, u[1:4]) and np.array_equal(it3, it[1:4])
+    ctx.close()
