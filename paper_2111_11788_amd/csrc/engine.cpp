@@ -516,7 +516,11 @@ int solve_impl(mlmc_ctx* ctx, SolveWork& w, const double* kap, double* u, int32_
   if (w.precision == MLMC_PREC_FP64) {
     auto& L = w.L64;
     L[0].kap = const_cast<double*>(kap);
-    if (w.exec_kap != kap || w.exec_u != u) w.release_graphs();
+    hipGraphExec_t* graph = &w.iter_exec[0];
+    if (w.exec_kap != kap || w.exec_u != u) {
+      w.release_graphs();
+      graph = nullptr;
+    }
     w.exec_kap = kap;
     w.exec_u = u;
     for (size_t l = 1; l < L.size(); ++l)
@@ -532,7 +536,7 @@ int solve_impl(mlmc_ctx* ctx, SolveWork& w, const double* kap, double* u, int32_
     for (int round = 0; round < 4 && total_it < ctx->cfg.max_iter; ++round) {
       int it = 0;
       if (int rc = pcg<double>(ctx, L, B, O, u, w.r, w.p, w.q, rtol, ctx->cfg.max_iter - total_it, &it,
-                              &w.iter_exec[0], w.p2, false, false, w.r2))
+                              graph, w.p2, false, false, w.r2))
         return rc;
       total_it += it;
       // confirm with the true residual; samples above tolerance continue

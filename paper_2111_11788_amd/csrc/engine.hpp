@@ -121,8 +121,9 @@ struct SolveWork {
   StateBufs outer, inner;
   // captured PCG iteration per precision (0: fp64, 1: fp32); tied to the buffers above
   hipGraphExec_t iter_exec[2] = {nullptr, nullptr};
-  // the caller's kappa and solution the fp64 iteration was captured with (a
-  // step-level solve may come with others: the iteration is captured again)
+  // the caller's kappa and solution of the last fp64 solve: its captured
+  // iteration holds them, so it is captured (and replayed) by a solve that comes
+  // with the arrays of the one before; a solve on others launches eagerly
   const double* exec_kap = nullptr;
   const double* exec_u = nullptr;
 
@@ -206,6 +207,8 @@ struct MeshWork {
     u = cv.take<double>((size_t)B * grid_stride(n));
     q = cv.take<double>(B);
     sw.carve(cv, n, B, c.precision, c.solver);
+    sw.exec_kap = kap;   // a lane's arrays stay where they are
+    sw.exec_u = u;
     if (c.forcing == MLMC_FORCING_LOGNORMAL) {
       xif = cv.take<double>((size_t)B * c.n_modes);
       fe = cv.take<double>((size_t)B * elem_count(n));
