@@ -450,9 +450,10 @@ enum {
   MLMC_FUSE_RUPDATE = 64   /* with DIRECTION and PRESMOOTH: the PCG update r -= alpha q is formed inside
                               the next iteration's first V-cycle kernel (residual restriction), which
                               writes r to the other of two residual buffers and tests convergence */,
-  MLMC_FUSE_SOLVE = 128,   /* mixed precision with GMG on a 4^3 or 8^3 mesh: the whole solve of a sample
-                              (fp64 refinement, fp32 PCG, V-cycle) in one workgroup with every vector in
-                              LDS, one launch per batch; needs vsmall_fp32 >= the mesh */
+  MLMC_FUSE_SOLVE = 128,   /* the whole solve of a sample in one workgroup, its vectors in registers and LDS,
+                              one launch per batch: mixed precision with GMG on a 4^3 to 16^3 mesh (fp64
+                              refinement, fp32 PCG, V-cycle; needs vsmall_fp32 >= the mesh), fp64 with GMG
+                              where vsmall_fp64 >= the mesh, fp64 with Jacobi up to 16^3 */
   MLMC_FUSE_PACK = 256     /* sampling rounds: the solves of two levels on the same mesh (level l's own
                               and level l+1's coarse one) share one batched solve when together they fit
                               the lane capacity of that mesh */

@@ -513,7 +513,15 @@ int solve_impl(mlmc_ctx* ctx, SolveWork& w, const double* kap, double* u, int32_
   LAUNCH(MLMC_K_MISC, 0, launch_set_active(B, O, 1, st));
   HIPCHK(hipMemsetAsync(O.iters, 0, B * sizeof(int), st));
   int total_it = 0;
-  if (w.precision == MLMC_PREC_FP64) {
+  const bool gmg = ctx->cfg.solver == MLMC_SOLVER_GMG_PCG;
+  if (w.precision == MLMC_PREC_FP64 && (ctx->fuse & MLMC_FUSE_SOLVE) && n >= 4 &&
+      n <= (gmg ? ctx->vsmall_n0[0] : 16)) {
+    // the whole solve of each sample in one workgroup
+    const ChebCoeffs& ch = ctx->cheb;
+    LAUNCH(MLMC_K_SOLVE_SMALL, (e * 8 + d * 8 * (bvec ? 2 : 1)),
+           launch_solve_small64(n, B, gmg, ch.degree, ch.c1, ch.c2, kap, bvec, h3, u, O.active, O.iters, rtol,
+                                ctx->cfg.max_iter, kMaxConfirm, st, O.rr));
+  } else if (w.precision == MLMC_PREC_FP64) {
     auto& L = w.L64;
     L[0].kap = const_cast<double*>(kap);
     hipGraphExec_t* graph = &w.iter_exec[0];
@@ -533,7 +541,7 @@ int solve_impl(mlmc_ctx* ctx, SolveWork& w, const double* kap, double* u, int32_
       LAUNCH(MLMC_K_MISC, d * 8, launch_fill_interior<double>(n, B, w.r, h3, nullptr, st));
     LAUNCH(MLMC_K_PCG_DOT, 2 * d * 8, (launch_dot<double>(n, B, w.r, w.r, O, &np, st)));
     LAUNCH(MLMC_K_REDUCE, 0, launch_reduce(B, RED_BB, 0.0, np, O, nullptr, st));
-    for (int round = 0; round < 4 && total_it < ctx->cfg.max_iter; ++round) {
+    for (int round = 0; round < kMaxConfirm && total_it < ctx->cfg.max_iter; ++round) {
       int it = 0;
       if (int rc = pcg<double>(ctx, L, B, O, u, w.r, w.p, w.q, rtol, ctx->cfg.max_iter - total_it, &it,
                               graph, w.p2, false, false, w.r2))
@@ -548,8 +556,7 @@ int solve_impl(mlmc_ctx* ctx, SolveWork& w, const double* kap, double* u, int32_
       if (int rc = count_active(ctx, O, B, &na)) return rc;
       if (na == 0) break;
     }
-  } else if ((ctx->fuse & MLMC_FUSE_SOLVE) && ctx->cfg.solver == MLMC_SOLVER_GMG_PCG && (n == 4 || n == 8) &&
-             ctx->vsmall_n0[1] >= n) {
+  } else if ((ctx->fuse & MLMC_FUSE_SOLVE) && ctx->cfg.solver == MLMC_SOLVER_GMG_PCG && n >= 4 && ctx->vsmall_n0[1] >= n) {
     // the whole solve of each sample in one workgroup (all vectors in LDS)
     const ChebCoeffs& ch = ctx->cheb;
     LAUNCH(MLMC_K_SOLVE_SMALL, (e * 8 + d * 8 * (bvec ? 2 : 1)),

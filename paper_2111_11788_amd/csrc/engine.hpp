@@ -42,6 +42,7 @@ constexpr double kChebHi = 1.75;
 constexpr double kChebRatio = 4.0;   // smoothing interval [hi / ratio, hi]
 constexpr double kInnerRtol = 1e-4;  // fp32 inner solve tolerance (mixed precision)
 constexpr int kMaxOuter = 30;
+constexpr int kMaxConfirm = 4;        // fp64: solves to the recurrence's tolerance before the true residual is given up
 constexpr int kMaxLevelBatch = 65536;   // samples per batch on a coarse level (see level_cap)
 
 inline size_t align256(size_t b) { return (b + 255) / 256 * 256; }

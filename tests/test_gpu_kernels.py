@@ -93,3 +93,70 @@ def test_split_planes_leave_a_samples_bits(n, B, prec, deg):
     u3, it3 = ctx.solve(n, kap[1:4].contiguous())
     assert torch.equal(u3, u[1:4]) and np.array_equal(it3, it[1:4])
     ctx.close()
+
+
+# whole solves in one workgroup against the level-by-level kernels, both to a
+# true relative residual of 1e-12: the iterates differ by at most the condition
+# number of the Jacobi-scaled operator (~ n^2 times the contrast of kappa,
+# below 1e4) times twice that
+@pytest.mark.parametrize("n", [4, 8, 16])
+@pytest.mark.parametrize("prec,solver,deg", [(0, 0, 1), (0, 0, 3), (0, 1, 1), (1, 0, 1), (1, 0, 2), (1, 0, 3)])
+def test_whole_solves_match_the_level_kernels(n, prec, solver, deg):
+    ctx = mm.Context(_wl(n0=n, precision=prec, solver=solver), cheb_degree=deg, arena_bytes=256 << 20)
+    kap = ctx.field(n, ctx.draw_xi(0, 3, 5))
+    fuse = ctx.tuning()["fuse"]
+    got = {}
+    for f in (fuse | mm.FUSE_SOLVE, fuse & ~mm.FUSE_SOLVE):
+        ctx.set_tuning(fuse=f)
+        got[f] = ctx.solve(n, kap)
+    (u, it), (w, iw) = got.values()
+    assert float((u - w).norm() / w.norm()) <= 2e-8
+    assert np.abs(it - iw).max() <= 1
+    # a sample alone, and boundary positions
+    ctx.set_tuning(fuse=fuse | mm.FUSE_SOLVE)
+    assert torch.equal(ctx.solve(n, kap[2:3].contiguous())[0][0], u[2])
+    assert float(u.abs().sum()) == pytest.approx(float(mm.from_grid(u, n).abs().sum()), rel=1e-15)
+    ctx.close()
+
+
+@pytest.mark.parametrize("n", [4, 8, 16])
+@pytest.mark.parametrize("prec,solver", [(0, 0), (0, 1), (1, 0)])
+def test_whole_solves_report_their_status(n, prec, solver):
+    # a NaN coefficient ends its own sample only; a cap of 2 iterations is reported
+    wl = _wl(n0=n, precision=prec, solver=solver)
+    ctx = mm.Context(wl, arena_bytes=256 << 20)
+    kap = ctx.field(n, ctx.draw_xi(0, 3, 4))
+    good, _ = ctx.solve(n, kap)
+    kap[1, 5] = float("nan")
+    u = torch.zeros_like(good)
+    it = np.zeros(4, dtype=np.int32)
+    rc = mm.lib().mlmc_solve(ctx.h, n, 4, kap.data_ptr(), u.data_ptr(), it.ctypes.data)
+    assert rc == -5   # MLMC_E_NONFINITE
+    assert torch.equal(u[[0, 2, 3]], good[[0, 2, 3]])
+    ctx.close()
+    short = mm.Context(wl, arena_bytes=256 << 20, max_iter=2)
+    xi = short.draw_xi(0, 3, 4)
+    _, it = short.solve(n, short.field(n, xi), allow_noconv=True)
+    assert it.max() <= 2
+    with pytest.raises(mm.MLMCError) as e:
+        short.solve(n, short.field(n, xi))
+    assert e.value.code == -4
+    short.close()
+
+
+# the coarse end of the V-cycle (and with it the 16^3 preconditioner) keeps the
+# level-by-level result: fp32 rounding of a few steps apart
+@pytest.mark.parametrize("n,deg", [(4, 1), (8, 2), (16, 1), (16, 2), (16, 4), (32, 2)])
+@pytest.mark.parametrize("prec", [0, 1])
+def test_single_kernel_vcycle_matches_the_level_kernels(n, deg, prec):
+    ctx = mm.Context(_wl(n0=n), cheb_degree=deg, arena_bytes=256 << 20)
+    dt = torch.float64 if prec == 0 else torch.float32
+    g = torch.Generator(device="cuda").manual_seed(n + deg)
+    kap = torch.exp(torch.randn((3, n ** 3), generator=g, dtype=torch.float64, device="cuda")).to(dt)
+    r = mm.to_grid(torch.randn((3, (n - 1) ** 3), generator=g, dtype=torch.float64, device="cuda").to(dt), n)
+    f = ctx.vcycle if prec == 0 else ctx.vcycle_f32
+    z = f(n, kap, r)
+    ctx.set_tuning(vsmall_fp32=0, vsmall_fp64=0)
+    w = f(n, kap, r)
+    assert float((z - w).norm() / w.norm()) <= (1e-13 if prec == 0 else 2e-5)
+    ctx.close()
