@@ -20,11 +20,11 @@ hipError_t launch_load(int n, int B, const double* f, double* b, hipStream_t st)
 // every interior node.  Writes u (grid layout), active (0 where converged to
 // rtol) and iters (inner iterations); rr_out (may be null) the last fp64
 // ||b - A u||^2.  A NaN or Inf residual ends a sample's solve (active 0, rr_out
-// non-finite).
+// non-finite).  rows (may be null): solve r is batch slot rows[r] of every array.
 hipError_t launch_solve_small(int n, int B, int degree, const double* c1, const double* c2, const double* kap,
                               const double* bvec, double bconst, double* u, int* active, int* iters, double rtol,
                               double inner_rtol, int max_iter, int max_outer, hipStream_t st,
-                              double* rr_out = nullptr);
+                              double* rr_out = nullptr, const int* rows = nullptr);
 // The whole fp64 solve likewise: PCG to rtol on the recurrence, preconditioned
 // by the V-cycle (gmg; n = 4 or 8) or by the diagonal (n = 4, 8 or 16),
 // confirmed by the true residual at most max_outer times.

@@ -173,6 +173,54 @@ int setup_slots(Pool& p, int c) {
   return MLMC_OK;
 }
 
+// Pools of meshes up to 16^3 run a slot's whole solve in the step that admits
+// it, one workgroup per solve (MLMC_FUSE_SOLVE), instead of one inner iteration
+// of every slot per step: ~30 launches of a few microseconds per iteration for
+// a mesh whose solve takes 50 to 150 us (400 requests over 16^3 to 64^3:
+// SERVE_NOW).
+bool whole_solves(const Pool& p) {
+  return (p.sub.fuse & MLMC_FUSE_SOLVE) && p.n >= 4 && p.n <= p.sub.vsmall_n0[1];
+}
+
+// Draw, field, solve and QoI of the `c` new jobs in p.h_slots[0..c); h_phase
+// receives PHASE_DONE where a slot converged (or its residual became NaN or
+// Inf), PHASE_FREE where it did not.
+int step_whole(Pool& p, int c) {
+  mlmc_ctx* ctx = &p.sub;
+  hipStream_t st = ctx->st;
+  const int S = p.S, n = p.n;
+  const double h = 1.0 / n;
+  HIPCHK(hipMemcpyAsync(p.d_ids, p.h_ids, c * sizeof(uint64_t), hipMemcpyHostToDevice, st));
+  HIPCHK(hipMemcpyAsync(p.d_lv, p.h_lv, c * sizeof(int), hipMemcpyHostToDevice, st));
+  HIPCHK(hipMemcpyAsync(p.d_slots, p.h_slots, c * sizeof(int), hipMemcpyHostToDevice, st));
+  HIPCHK(hipMemsetAsync(p.m_new, 0, S * sizeof(int), st));
+  SRV_LAUNCH(launch_set_phase_list(c, p.d_slots, p.m_new, 1, st));
+  SRV_LAUNCH(launch_draw_xi_rows(ctx->cfg.seed, c, ctx->cfg.n_modes, p.d_ids, p.d_lv, p.d_slots, p.xi, st));
+  double* tab = nullptr;
+  if (int rc = ensure_tables(ctx, n, &tab)) return rc;
+  SRV_LAUNCH(launch_field(n, ctx->cfg.n_modes, c, p.xi, ctx->d_sqrtlam, ctx->d_triples, tab, ctx->K1, p.kap64,
+                          nullptr, st, p.d_slots, ctx->cfg.precision == MLMC_PREC_MIXED_BF16KLE,
+                          field_separable(ctx, c) ? ctx->d_xperm : nullptr, ctx->d_xoff));
+  // as many iterations as the steps after which a slot is given up (pool_loop)
+  const int cap = ctx->cfg.max_iter > (1 << 28) ? 1 << 30 : 4 * ctx->cfg.max_iter;
+  const ChebCoeffs& ch = ctx->cheb;
+  SRV_LAUNCH(launch_solve_small(n, c, ch.degree, ch.c1, ch.c2, p.kap64, nullptr, h * h * h, p.u, p.w.outer.s.active,
+                                p.w.inner.s.iters, ctx->cfg.rtol, kInnerTol, cap, kMaxOuter, st, nullptr, p.d_slots));
+  SolveState dn = view(p.w.outer.s, p.m_new, p.phase);
+  uint32_t np = 0;
+  SRV_LAUNCH(launch_qoi_partial(n, S, ctx->cfg.qoi, p.u, dn, &np, st, true));
+  SRV_LAUNCH(launch_reduce(S, RED_STORE, 0.0, np, dn, p.q, st));
+  HIPCHK(hipMemcpyAsync(p.h_phase, p.w.outer.s.active, S * sizeof(int), hipMemcpyDeviceToHost, st));
+  HIPCHK(hipMemcpyAsync(p.h_q, p.q, S * sizeof(double), hipMemcpyDeviceToHost, st));
+  HIPCHK(hipMemcpyAsync(p.h_iters, p.w.inner.s.iters, S * sizeof(int), hipMemcpyDeviceToHost, st));
+  HIPCHK(hipStreamSynchronize(st));
+  for (int r = 0; r < c; ++r) {
+    int& ph = p.h_phase[p.h_slots[r]];
+    ph = ph ? PHASE_FREE : PHASE_DONE;
+  }
+  return MLMC_OK;
+}
+
 int masks(Pool& p) {
   mlmc_ctx* ctx = &p.sub;
   SRV_LAUNCH(launch_phase_masks(p.S, p.phase, p.w.inner.s.active, p.m_trans, p.m_restart, p.m_done, ctx->st));
@@ -372,6 +420,7 @@ bool reclaim(mlmc_server* srv, Pool* L, std::unique_lock<std::mutex>& lk) {
 
 void pool_loop(mlmc_server* srv, Pool* p) {
   const int max_iter = srv->ctx->cfg.max_iter;
+  const bool whole = whole_solves(*p);
   std::vector<int> steps(p->S, 0);
   Pool* src = p->owner ? p->owner : p;   // the pool whose queue feeds these slots
   for (;;) {
@@ -410,8 +459,13 @@ void pool_loop(mlmc_server* srv, Pool* p) {
       }
     }
     const double t_step = srv->now();
-    int rc = c ? setup_slots(*p, c) : MLMC_OK;
-    if (!rc) rc = step(*p);
+    int rc = MLMC_OK;
+    if (whole) {
+      if (c) rc = step_whole(*p, c);
+    } else {
+      if (c) rc = setup_slots(*p, c);
+      if (!rc) rc = step(*p);
+    }
     std::lock_guard<std::mutex> lk(srv->mu);
     src->busy_slot_s += (double)p->occupied * (srv->now() - t_step);   // a guest's slots count for its mesh
     if (rc) {
@@ -427,7 +481,8 @@ void pool_loop(mlmc_server* srv, Pool* p) {
       if (!p->busy[s]) continue;
       steps[s]++;
       const bool done = p->h_phase[s] == PHASE_DONE;
-      const bool stuck = !done && steps[s] > 4 * max_iter;   // safety net: never converging
+      // safety net: never converging (a whole solve took as many iterations at most)
+      const bool stuck = !done && (whole || steps[s] > 4 * max_iter);
       if (!done && !stuck) continue;
       const Job& j = p->job[s];
       auto it = srv->reqs.find(j.ticket);

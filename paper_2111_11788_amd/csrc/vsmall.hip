@@ -628,10 +628,10 @@ template <int NL>
 __global__ void __launch_bounds__(small_threads<NL>(), NL == 2 ? 1 : 4) k_solve_small(SolveSmallArgs a, const double* __restrict__ kap,
                                                      const double* __restrict__ bvec, double* __restrict__ uglob,
                                                      int* __restrict__ active, int* __restrict__ iters,
-                                                     double* __restrict__ rr_out) {
+                                                     double* __restrict__ rr_out, const int* __restrict__ rows) {
   constexpr int n = 1 << NL, n2 = n * n, ne = n2 * n, TPB = small_threads<NL>();
   constexpr int S = lds_stride(n);
-  const int smp = blockIdx.x, tid = (int)threadIdx.x;
+  const int smp = rows ? rows[blockIdx.x] : (int)blockIdx.x, tid = (int)threadIdx.x;
   extern __shared__ __align__(32) unsigned char smem[];
   __shared__ double ws[2][16];
   Levels<float, NL> lv;
@@ -860,7 +860,8 @@ hipError_t launch_vsmall(int n0, int B, int degree, const double* c1, const doub
 
 hipError_t launch_solve_small(int n, int B, int degree, const double* c1, const double* c2, const double* kap,
                               const double* bvec, double bconst, double* u, int* active, int* iters, double rtol,
-                              double inner_rtol, int max_iter, int max_outer, hipStream_t st, double* rr_out) {
+                              double inner_rtol, int max_iter, int max_outer, hipStream_t st, double* rr_out,
+                              const int* rows) {
   if (degree < 1 || degree > 16 || B <= 0) return hipErrorInvalidValue;
   SolveSmallArgs a{};
   a.v = small_args(n, degree, c1, c2);
@@ -871,7 +872,7 @@ hipError_t launch_solve_small(int n, int B, int degree, const double* c1, const 
   a.max_outer = max_outer;
   const size_t lds = levels_bytes<float>(n);
 #define MLMC_SMALL(NL) \
-  k_solve_small<NL><<<dim3(B), dim3(small_threads<NL>()), lds, st>>>(a, kap, bvec, u, active, iters, rr_out)
+  k_solve_small<NL><<<dim3(B), dim3(small_threads<NL>()), lds, st>>>(a, kap, bvec, u, active, iters, rr_out, rows)
   if (n == 4) MLMC_SMALL(2);
   else if (n == 8) MLMC_SMALL(3);
   else if (n == 16) MLMC_SMALL(4);
