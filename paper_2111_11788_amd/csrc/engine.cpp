@@ -302,11 +302,13 @@ int precondition(mlmc_ctx* ctx, std::vector<Level<T>>& L, int B, const T* r, T**
   return vcycle<T>(ctx, L, 0, B, r, L[0].x, L[0].xo, L[0].t, S.active, z, &S, fused_np, zero_done, ru);
 }
 
-int count_active(mlmc_ctx* ctx, SolveState& s, int B, int* out) {
-  LAUNCH(MLMC_K_MISC, 0, launch_count_active(B, s, ctx->st));
-  HIPCHK(hipMemcpyAsync(ctx->h_nactive, s.nactive, sizeof(int), hipMemcpyDeviceToHost, ctx->st));
-  HIPCHK(hipStreamSynchronize(ctx->st));
-  *out = *ctx->h_nactive;
+int reduce_and_count(mlmc_ctx* ctx, SolveState& S, int B, int op, double tol2, uint32_t np) {
+  const bool merged = B <= kCountInReduce;
+  LAUNCH(MLMC_K_REDUCE, 0, launch_reduce(B, op, tol2, np, S, nullptr, ctx->st, merged ? ctx->h_nactive : nullptr));
+  if (!merged) {
+    LAUNCH(MLMC_K_MISC, 0, launch_count_active(B, S, ctx->st));
+    HIPCHK(hipMemcpyAsync(ctx->h_nactive, S.nactive, sizeof(int), hipMemcpyDeviceToHost, ctx->st));
+  }
   return MLMC_OK;
 }
 
@@ -332,15 +334,15 @@ int pcg_iteration(mlmc_ctx* ctx, std::vector<Level<T>>& L, int B, SolveState& S,
             launch_pcg_update_zero<T>(n, B, L[0].kap, x, p, r, q, L[0].x, ctx->cheb.c2[0], S, &np, st, var));
   else
     LAUNCHM(kid<T>(MLMC_K_PCG_UPDATE), 6 * d * sz, S.active, B, launch_pcg_update<T>(n, B, x, p, r, q, S, &np, st));
-  LAUNCH(MLMC_K_REDUCE, 0, launch_reduce(B, rr_op, tol2, np, S, nullptr, st));
+  if (count) {
+    if (int rc = reduce_and_count(ctx, S, B, rr_op, tol2, np)) return rc;
+  } else {
+    LAUNCH(MLMC_K_REDUCE, 0, launch_reduce(B, rr_op, tol2, np, S, nullptr, st));
+  }
   if (int rc = precondition<T>(ctx, L, B, r, &z, S, &np, fz)) return rc;
   if (!np) LAUNCHM(kid<T>(MLMC_K_PCG_DOT), 2 * d * sz, S.active, B, (launch_dot<T>(n, B, r, z, S, &np, st)));
   LAUNCH(MLMC_K_REDUCE, 0, launch_reduce(B, RED_BETA, 0.0, np, S, nullptr, st));
   LAUNCHM(kid<T>(MLMC_K_PCG_DIRECTION), 3 * d * sz, S.active, B, launch_pcg_direction<T>(n, B, z, p, S, st));
-  if (count) {
-    LAUNCH(MLMC_K_MISC, 0, launch_count_active(B, S, st));
-    HIPCHK(hipMemcpyAsync(ctx->h_nactive, S.nactive, sizeof(int), hipMemcpyDeviceToHost, st));
-  }
   return MLMC_OK;
 }
 
@@ -401,9 +403,9 @@ int pcg_iteration_dir(mlmc_ctx* ctx, std::vector<Level<T>>& L, int B, SolveState
               launch_pcg_rupdate_zero<T>(n, B, L[0].kap, r, q, L[0].x, ctx->cheb.c2[0], S, &np, st, var));
     else
       LAUNCHM(kid<T>(MLMC_K_PCG_UPDATE), 3 * d * sz, S.active, B, launch_pcg_rupdate<T>(n, B, r, q, S, &np, st));
+    if (count) return reduce_and_count(ctx, S, B, rr_op, tol2, np);
     LAUNCH(MLMC_K_REDUCE, 0, launch_reduce(B, rr_op, tol2, np, S, nullptr, st));
-  }
-  if (count) {
+  } else if (count) {   // the convergence test was inside the V-cycle
     LAUNCH(MLMC_K_MISC, 0, launch_count_active(B, S, st));
     HIPCHK(hipMemcpyAsync(ctx->h_nactive, S.nactive, sizeof(int), hipMemcpyDeviceToHost, st));
   }
@@ -551,10 +553,9 @@ int solve_impl(mlmc_ctx* ctx, SolveWork& w, const double* kap, double* u, int32_
       LAUNCH(MLMC_K_MISC, 0, launch_set_active(B, O, 1, st));
       LAUNCHM(MLMC_K_TRUE_RESIDUAL, ((bvec ? 3 : 2) * d + e) * 8, O.active, B,
               launch_true_residual(n, B, kap, h3, u, w.r, O, &np, st, zv<double>(ctx), bvec));
-      LAUNCH(MLMC_K_REDUCE, 0, launch_reduce(B, RED_RR, rtol * rtol, np, O, nullptr, st));
-      int na = 0;
-      if (int rc = count_active(ctx, O, B, &na)) return rc;
-      if (na == 0) break;
+      if (int rc = reduce_and_count(ctx, O, B, RED_RR, rtol * rtol, np)) return rc;
+      HIPCHK(hipStreamSynchronize(st));
+      if (*ctx->h_nactive == 0) break;
     }
   } else if ((ctx->fuse & MLMC_FUSE_SOLVE) && ctx->cfg.solver == MLMC_SOLVER_GMG_PCG && n >= 4 && ctx->vsmall_n0[1] >= n) {
     // the whole solve of each sample in one workgroup (all vectors in LDS)
@@ -619,12 +620,11 @@ int solve_impl(mlmc_ctx* ctx, SolveWork& w, const double* kap, double* u, int32_
           LAUNCHM(MLMC_K_TRUE_RESIDUAL, ((ucur ? 8 : 0) + 4 + 8 + 4 + bb_bytes) * d + 8 * e, O.active, B,
                   launch_refine(n, B, kap, h3, ucur, w.d, uout, w.rin, O, &np, st, zv<double>(ctx), bvec));
         LAUNCH(MLMC_K_MISC, 0, launch_set_phase_mask(B, O.active, w.alt, uout == w.r64 ? 1 : 0, nullptr, st));
-        LAUNCH(MLMC_K_REDUCE, 0, launch_reduce(B, RED_RR, rtol * rtol, np, O, nullptr, st));
+        if (int rc = reduce_and_count(ctx, O, B, RED_RR, rtol * rtol, np)) return rc;
         ucur = uout;
         next ^= 1;
-        int na = 0;
-        if (int rc = count_active(ctx, O, B, &na)) return rc;
-        if (na == 0) break;
+        HIPCHK(hipStreamSynchronize(st));
+        if (*ctx->h_nactive == 0) break;
       }
       SolveState moved = O;
       moved.active = w.alt;
@@ -654,10 +654,9 @@ int solve_impl(mlmc_ctx* ctx, SolveWork& w, const double* kap, double* u, int32_
         LAUNCHM(MLMC_K_MISC, d * 20, O.active, B, launch_add_correction(n, B, u, w.d, O, st));
         LAUNCHM(MLMC_K_TRUE_RESIDUAL, (2 * d + e) * 8, O.active, B,
                 launch_true_residual(n, B, kap, h3, u, w.r64, O, &np, st, zv<double>(ctx), bvec));
-        LAUNCH(MLMC_K_REDUCE, 0, launch_reduce(B, RED_RR, rtol * rtol, np, O, nullptr, st));
-        int na = 0;
-        if (int rc = count_active(ctx, O, B, &na)) return rc;
-        if (na == 0) break;
+        if (int rc = reduce_and_count(ctx, O, B, RED_RR, rtol * rtol, np)) return rc;
+        HIPCHK(hipStreamSynchronize(st));
+        if (*ctx->h_nactive == 0) break;
       }
     }
     // report inner iterations as the sample's iteration count

@@ -104,7 +104,8 @@ struct StateBufs {
     s.partial = cv.take<double>((size_t)B * s.pstride);
     s.active = cv.take<int>(B);
     s.iters = cv.take<int>(B);
-    s.nactive = cv.take<int>(1);
+    s.nactive = cv.take<int>(4);   // and the ticket, in the same 256 bytes
+    s.ticket = reinterpret_cast<unsigned long long*>(s.nactive + 2);
     s.pstate = cv.take<int>(B);
     s.began = cv.take<int>(B);
   }
@@ -475,7 +476,10 @@ int precondition(mlmc_ctx* ctx, std::vector<Level<T>>& L, int B, const T* r, T**
 // through the level-by-level kernels, so a PCG update can produce it.
 template <class T>
 bool zero_step_fusable(const mlmc_ctx* ctx, const std::vector<Level<T>>& L, int B);
-int count_active(mlmc_ctx* ctx, SolveState& s, int B, int* out);
+// The convergence test `op` on the partial sums of r . r, and the number of
+// samples still active to ctx->h_nactive (valid after the stream's next
+// synchronisation).
+int reduce_and_count(mlmc_ctx* ctx, SolveState& S, int B, int op, double tol2, uint32_t np);
 template <class T>
 int pcg_iteration(mlmc_ctx* ctx, std::vector<Level<T>>& L, int B, SolveState& S, T* x, T* r, T* p, T* q,
                   double tol2, int rr_op = RED_RR, bool count = true);

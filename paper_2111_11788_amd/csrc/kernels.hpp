@@ -61,6 +61,7 @@ struct SolveState {
   int* active;      // 1 while the sample iterates
   int* iters;       // iterations done
   int* nactive;     // single counter (device) of active samples
+  unsigned long long* ticket;   // zero between launches: how a reduction's workgroups find the last of them
   uint32_t pstride; // capacity of partial sums per sample
   int* phase;       // serving: per-slot phase (PHASE_*), may be null
   int* pstate;      // fused-direction PCG: bit 0 = buffer of the current direction, bit 1 = no step taken yet,
@@ -250,8 +251,13 @@ enum ReduceOp : int {
 // The RR ops treat a NaN or Inf sum as the end of the sample's solve (active
 // 0, or the DONE / TRANSITION phase), keeping the value in rr so the caller can
 // tell it from convergence.
+// h_count (may be null; pinned host memory): receives the number of samples
+// active after the op, for B <= kCountInReduce samples.
 hipError_t launch_reduce(int B, int op, double tol2, uint32_t nparts, SolveState s, double* out,
-                         hipStream_t st);
+                         hipStream_t st, int* h_count = nullptr);
+// above this a reduction's workgroups would queue on the counter for longer
+// than the separate count takes (~2 ns each against two launches of ~4 us)
+constexpr int kCountInReduce = 4096;
 
 // Chan, Golub and LeVeque merge of the summary (nb, mb, m2b) into (n, mean, m2)
 __host__ __device__ inline void chan_merge(double& n, double& mean, double& m2, double nb, double mb, double m2b) {

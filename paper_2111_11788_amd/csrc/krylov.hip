@@ -291,15 +291,8 @@ __global__ void __launch_bounds__(kBlock) k_qoi_subcube(int n, uint32_t chunks, 
   if (threadIdx.x == 0) st.partial[(size_t)b * st.pstride + c] = acc;
 }
 
-// one workgroup per sample: fixed-order sum of its partials, then the scalar op
-__global__ void __launch_bounds__(kBlock) k_reduce(int op, double tol2, uint32_t nparts, SolveState st, double* out) {
-  const int b = blockIdx.x;
-  if (op != RED_STORE && st.active && !st.active[b]) return;
-  const double* p = st.partial + (size_t)b * st.pstride;
-  double v = 0.0;
-  for (uint32_t c = threadIdx.x; c < nparts; c += kBlock) v += p[c];
-  v = block_sum(v);
-  if (threadIdx.x != 0) return;
+// The scalar op of sample b on the sum v of its partials
+__device__ __forceinline__ void reduce_op(int op, double tol2, const SolveState& st, double* out, int b, double v) {
   switch (op) {
     case RED_BB: st.bb[b] = v; break;
     case RED_ALPHA: st.alpha[b] = st.rz[b] / v; st.iters[b] += 1; break;
@@ -343,6 +336,59 @@ __global__ void __launch_bounds__(kBlock) k_reduce(int op, double tol2, uint32_t
       st.phase[b] = (v <= tol2 * st.bb[b] || !isfinite(v)) ? PHASE_DONE : PHASE_RESTART;
       break;
     default: out[b] = v; break;
+  }
+}
+
+// `act` of this workgroup's samples are active after the op: the workgroups
+// add up their counts and their number in one word, and the last one hands the
+// total to the host (a pinned word the stream's next synchronisation makes
+// visible) and clears the word for the next launch.
+__device__ __forceinline__ void count_on_host(unsigned long long* ticket, int* h_count, int act) {
+  const unsigned long long old = atomicAdd(ticket, (1ull << 32) | (unsigned)act);
+  if ((unsigned)(old >> 32) + 1 == gridDim.x) {
+    __hip_atomic_store(h_count, (int)(unsigned)old + act, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    *ticket = 0;
+  }
+}
+
+// one workgroup per sample: fixed-order sum of its partials, then the scalar op
+__global__ void __launch_bounds__(kBlock) k_reduce(int op, double tol2, uint32_t nparts, SolveState st, double* out,
+                                                   int* h_count) {
+  const int b = blockIdx.x;
+  const bool on = op == RED_STORE || !st.active || st.active[b];
+  if (on) {   // uniform over the workgroup
+    const double* p = st.partial + (size_t)b * st.pstride;
+    double v = 0.0;
+    for (uint32_t c = threadIdx.x; c < nparts; c += kBlock) v += p[c];
+    v = block_sum(v);
+    if (threadIdx.x == 0) reduce_op(op, tol2, st, out, b, v);
+  }
+  if (h_count && threadIdx.x == 0) count_on_host(st.ticket, h_count, st.active[b] != 0);
+}
+
+// one wave per sample, for at most 64 partials: the same sum (the other waves
+// of k_reduce add zeros), a quarter of the workgroups
+__global__ void __launch_bounds__(kBlock) k_reduce_wave(int B, int op, double tol2, uint32_t nparts, SolveState st,
+                                                        double* out, int* h_count) {
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int b = blockIdx.x * (kBlock / 64) + wave;
+  __shared__ int act[kBlock / 64];
+  const bool in = b < B;
+  const bool on = in && (op == RED_STORE || !st.active || st.active[b]);
+  if (on) {   // uniform over the wave
+    double v = (uint32_t)lane < nparts ? st.partial[(size_t)b * st.pstride + lane] : 0.0;
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
+    if (lane == 0) reduce_op(op, tol2, st, out, b, v);
+  }
+  if (!h_count) return;
+  if (lane == 0) act[wave] = in && st.active[b] != 0;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    int t = 0;
+#pragma unroll
+    for (int w = 0; w < kBlock / 64; ++w) t += act[w];
+    count_on_host(st.ticket, h_count, t);
   }
 }
 
@@ -613,8 +659,12 @@ hipError_t launch_level_stats(int njobs, const StatsJobs& jobs, hipStream_t st) 
   return hipGetLastError();
 }
 
-hipError_t launch_reduce(int B, int op, double tol2, uint32_t nparts, SolveState s, double* out, hipStream_t st) {
-  k_reduce<<<dim3(B), kBlock, 0, st>>>(op, tol2, nparts, s, out);
+hipError_t launch_reduce(int B, int op, double tol2, uint32_t nparts, SolveState s, double* out, hipStream_t st,
+                         int* h_count) {
+  if (nparts <= 64)
+    k_reduce_wave<<<dim3((B + kBlock / 64 - 1) / (kBlock / 64)), kBlock, 0, st>>>(B, op, tol2, nparts, s, out, h_count);
+  else
+    k_reduce<<<dim3(B), kBlock, 0, st>>>(op, tol2, nparts, s, out, h_count);
   return hipGetLastError();
 }
 
