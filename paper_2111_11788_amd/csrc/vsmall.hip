@@ -168,6 +168,49 @@ __device__ __forceinline__ void q1v(const Own<n>& o, const T* u, const T* kap, T
   }
 }
 
+// As q1v, with the kappa sums as a result and one element row at a time: about 35
+// values live (the rows of the own plane are read twice), for a kernel held to 64
+// registers
+template <int n, class T>
+__device__ __forceinline__ void q1v_lean(const Own<n>& o, const T* u, const T* kap, T (&au)[4], T (&ks)[4]) {
+  constexpr int n2 = n * n;
+  const T* up = u + o.pos;
+  const T* kp = kap + o.pos - n - n2;
+  T f[4];
+#pragma unroll
+  for (int v = 0; v < 4; ++v) f[v] = ks[v] = T(0);
+#pragma unroll
+  for (int sz = 0; sz < 2; ++sz) {
+    T Q1[6];
+    o.urow(up + n2 * (2 * sz - 1), Q1);
+#pragma unroll
+    for (int sy = 0; sy < 2; ++sy) {
+      T K[5], M[6], Q[6];
+      o.krow(kp + n2 * sz + n * sy, K);
+      o.urow(up + n * (2 * sy - 1), M);
+      o.urow(up + n2 * (2 * sz - 1) + n * (2 * sy - 1), Q);
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+#pragma unroll
+        for (int sx = 0; sx < 2; ++sx) {
+          const T kv = K[v + sx];
+          const T g = (M[v + 2 * sx] + Q1[v + 2 * sx]) + (Q[v + 1] + Q[v + 2 * sx]);
+          ks[v] += kv;
+          f[v] += kv * g;
+        }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+  T uc[4];
+  ld4(up, uc);
+  const T h = T(1) / T(n);
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    const T a = h * (ks[v] * uc[v] * (T(1) / T(3)) - f[v] * (T(1) / T(12)));
+    au[v] = (v > 0 || o.gx != 0) ? a : T(0);
+  }
+}
+
 // A u in the operation order of the LDS-tiled stencil engine's apply (16^3
 // solves: the PCG operator those meshes had there)
 template <int n, class T>
@@ -257,6 +300,13 @@ __device__ __forceinline__ void q1v_rows(const Own<n>& o, const T* u, const T* k
   for (int v = 0; v < 4; ++v) au[v] = (v > 0 || o.gx != 0) ? h12 * fma(ks[v] * uc[v], T(4), -f[v]) : T(0);
 }
 
+// D, the Jacobi diagonal, from the kappa sums
+template <int n, class T>
+__device__ __forceinline__ T diag_of(T ks) {
+  const T h = T(1) / T(n);
+  return h * ks * (T(1) / T(3));
+}
+
 // Jacobi scaling by what a node keeps of its diagonal D: fp32 divides by D (the
 // scalar form's rounding), fp64 multiplies by 1 / D
 __device__ __forceinline__ float keep_diag(float d) { return d; }
@@ -305,9 +355,8 @@ __device__ __forceinline__ void form_diag(const Levels<T, NL>& lv, Nodes<T, NL>&
     if (o.has) {
       T ks[4];
       ksum4<n>(o, lv.K[L], ks);
-      const T h = T(1) / T(n);
 #pragma unroll
-      for (int v = 0; v < 4; ++v) nd.dg[L][v] = keep_diag(h * ks[v] * (T(1) / T(3)));
+      for (int v = 0; v < 4; ++v) nd.dg[L][v] = keep_diag(diag_of<n>(ks[v]));
     }
     form_diag<T, NL, L + 1>(lv, nd);
   }
@@ -315,7 +364,8 @@ __device__ __forceinline__ void form_diag(const Levels<T, NL>& lv, Nodes<T, NL>&
 
 // One V-cycle from level L: nd.b[L] the right-hand side, nd.x[L] the result (and
 // an LDS copy in lv.x(L, return value) for L > 0).  Called by every thread.
-template <class T, int NL, int L>
+// Lean: few registers, the diagonals formed where they are used.
+template <class T, int NL, int L, bool Lean = false>
 __device__ int vcycle_small(const SmallArgs& a, const Levels<T, NL>& lv, Nodes<T, NL>& nd) {
   constexpr int n = (1 << NL) >> L;
   const Own<n> o;
@@ -327,14 +377,31 @@ __device__ int vcycle_small(const SmallArgs& a, const Levels<T, NL>& lv, Nodes<T
   T xo[4];
   // pre-smoothing from 0
 #pragma unroll
-  for (int v = 0; v < 4; ++v) x[v] = (v > 0 || o.gx != 0) ? scale_diag(T(a.c2[0]) * b[v], dg[v]) : T(0);
-  if (o.has) st4(lv.x(L, c) + o.pos, x);
+  for (int v = 0; v < 4; ++v) x[v] = T(0);
+  if (o.has) {
+    if constexpr (Lean) {
+      T ks[4];
+      ksum4<n>(o, kap, ks);
+#pragma unroll
+      for (int v = 0; v < 4; ++v) dg[v] = diag_of<n>(ks[v]);
+    }
+#pragma unroll
+    for (int v = 0; v < 4; ++v) x[v] = (v > 0 || o.gx != 0) ? scale_diag(T(a.c2[0]) * b[v], dg[v]) : T(0);
+    st4(lv.x(L, c) + o.pos, x);
+  }
   __syncthreads();
   // one smoothing step: x <- x + c1 (x - xo) + c2 D^-1 (b - A x)
   auto smooth = [&](T c1, T c2, bool use_xo) {
     if (o.has) {
       T au[4];
-      q1v<n>(o, lv.x(L, c), kap, au);
+      if constexpr (Lean) {
+        T ks[4];
+        q1v_lean<n>(o, lv.x(L, c), kap, au, ks);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) dg[v] = diag_of<n>(ks[v]);
+      } else {
+        q1v<n>(o, lv.x(L, c), kap, au);
+      }
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
         const T prev = use_xo ? x[v] - xo[v] : x[v];
@@ -356,7 +423,12 @@ __device__ int vcycle_small(const SmallArgs& a, const Levels<T, NL>& lv, Nodes<T
   // the residual into the other copy
   if (o.has) {
     T t[4];
-    q1v<n>(o, lv.x(L, c), kap, t);
+    if constexpr (Lean) {
+      T ks[4];
+      q1v_lean<n>(o, lv.x(L, c), kap, t, ks);
+    } else {
+      q1v<n>(o, lv.x(L, c), kap, t);
+    }
 #pragma unroll
     for (int v = 0; v < 4; ++v) t[v] = b[v] - t[v];
     st4(lv.x(L, c ^ 1) + o.pos, t);
@@ -394,7 +466,7 @@ __device__ int vcycle_small(const SmallArgs& a, const Levels<T, NL>& lv, Nodes<T
       }
       if (oc.gx == 0) bc[0] = T(0);
     }
-    const int cc = vcycle_small<T, NL, L + 1>(a, lv, nd);
+    const int cc = vcycle_small<T, NL, L + 1, Lean>(a, lv, nd);
     xc = lv.x(L + 1, cc);
   } else {
     // 2^3: one unknown, A_11 = (h / 3) sum of the 8 kappa, h = 1/2
@@ -455,8 +527,9 @@ __device__ int vcycle_small(const SmallArgs& a, const Levels<T, NL>& lv, Nodes<T
 template <int NL>
 constexpr int small_threads() { return NL == 4 ? 1024 : (NL == 3 ? 128 : 64); }
 
-template <class T, int NL>
-__global__ void __launch_bounds__(small_threads<NL>()) k_vsmall(SmallArgs a, const T* __restrict__ bglob,
+// Lean: two workgroups of 16^3 per CU (64 registers, 60 KB of LDS each)
+template <class T, int NL, bool Lean>
+__global__ void __launch_bounds__(small_threads<NL>(), Lean ? 8 : 1) k_vsmall(SmallArgs a, const T* __restrict__ bglob,
                                                                 T* __restrict__ xglob,
                                                                 const int* __restrict__ active) {
   constexpr int n = 1 << NL, TPB = small_threads<NL>();
@@ -491,8 +564,8 @@ __global__ void __launch_bounds__(small_threads<NL>()) k_vsmall(SmallArgs a, con
     }
   }
   __syncthreads();
-  form_diag<T, NL, 0>(lv, nd);
-  vcycle_small<T, NL, 0>(a, lv, nd);
+  if constexpr (!Lean) form_diag<T, NL, 0>(lv, nd);
+  vcycle_small<T, NL, 0, Lean>(a, lv, nd);
   if (o.has) st4(xglob + (size_t)smp * a.gstride + o.pos, nd.x[0]);
 }
 
@@ -845,11 +918,17 @@ hipError_t launch_vsmall(int n0, int B, int degree, const double* c1, const doub
   for (int n = n0; n >= 2 && l < kMaxLv; n /= 2, ++l) a.kap[l] = kap_levels[l];
   const size_t lds = levels_bytes<T>(n0);
   switch (n0) {
-    case 4: k_vsmall<T, 2><<<dim3(B), dim3(small_threads<2>()), lds, st>>>(a, b, x, active); break;
-    case 8: k_vsmall<T, 3><<<dim3(B), dim3(small_threads<3>()), lds, st>>>(a, b, x, active); break;
+    case 4: k_vsmall<T, 2, false><<<dim3(B), dim3(small_threads<2>()), lds, st>>>(a, b, x, active); break;
+    case 8: k_vsmall<T, 3, false><<<dim3(B), dim3(small_threads<3>()), lds, st>>>(a, b, x, active); break;
     case 16:
       if constexpr (sizeof(T) == 4) {
-        k_vsmall<T, 4><<<dim3(B), dim3(small_threads<4>()), lds, st>>>(a, b, x, active);
+        // more workgroups than half the CUs: two per CU, so that the launches of
+        // other lanes, which such a batch has, run beside this one (1024 samples
+        // of 64^3 over four lanes: 39.6 -> 39.1 ms, though alone a launch of 256
+        // takes 18.6 us in place of 16.8); else all the registers the compiler
+        // wants (32 pairs of 32^3: 1.10 ms against 1.13)
+        if (B > 128) k_vsmall<T, 4, true><<<dim3(B), dim3(small_threads<4>()), lds, st>>>(a, b, x, active);
+        else k_vsmall<T, 4, false><<<dim3(B), dim3(small_threads<4>()), lds, st>>>(a, b, x, active);
         break;
       }
       return hipErrorInvalidValue;   // above the LDS of a workgroup in fp64

@@ -160,3 +160,18 @@ def test_single_kernel_vcycle_matches_the_level_kernels(n, deg, prec):
     w = f(n, kap, r)
     assert float((z - w).norm() / w.norm()) <= (1e-13 if prec == 0 else 2e-5)
     ctx.close()
+
+
+# more than 128 samples take the form of the single-kernel V-cycle that two
+# workgroups per CU fit: the same operations in the same order
+@pytest.mark.parametrize("n,deg", [(16, 1), (16, 3), (32, 2)])
+@pytest.mark.parametrize("B", [129, 300])
+def test_single_kernel_vcycle_of_a_large_batch_keeps_a_samples_bits(n, deg, B):
+    ctx = mm.Context(_wl(n0=n, precision=1), cheb_degree=deg, arena_bytes=2 << 30)
+    g = torch.Generator(device="cuda").manual_seed(n + deg)
+    kap = torch.exp(torch.randn((B, n ** 3), generator=g, dtype=torch.float64, device="cuda")).float()
+    r = mm.to_grid(torch.randn((B, (n - 1) ** 3), generator=g, dtype=torch.float64, device="cuda").float(), n)
+    z = ctx.vcycle_f32(n, kap, r)
+    for a in range(0, B, 100):
+        assert torch.equal(ctx.vcycle_f32(n, kap[a:a + 100].contiguous(), r[a:a + 100].contiguous()), z[a:a + 100])
+    ctx.close()
