@@ -90,6 +90,19 @@ inline ZGeom zgeom(int n, int B) {
   return g;
 }
 
+// The geometry of zgeom for a row of 128 vectors (256^3 in fp64): 512 threads,
+// four rows.  256 threads would hold two, and stage four.
+template <class T>
+inline ZGeom zgeom_long(int n, int B) {
+  ZGeom g = zgeom<T>(n, B);
+  if (g.G != 128) return g;
+  g.threads = 512;
+  g.rows = 512 / g.G;
+  g.row_blocks = (n - 1 + g.rows - 1) / g.rows;
+  zsplit(g, (long)B * g.row_blocks * (g.threads / 64));
+  return g;
+}
+
 // The geometry of zgeom with `rows` rows per workgroup instead of the most
 // that fit (rows >= 1, same thread count).
 template <class T>

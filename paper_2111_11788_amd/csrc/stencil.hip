@@ -60,7 +60,7 @@ __device__ __forceinline__ double wave_sum63(double v) {
 // out = the workgroup's sum of v, taken by every thread of it (waves in
 // order).  Two calls need a barrier between them beyond the one in here.
 __device__ __forceinline__ void unit_sum(double v, double* out) {
-  __shared__ double wsum[kBlock / 64];
+  __shared__ double wsum[8];   // at most 512 threads
   v = wave_sum63(v);
   if ((threadIdx.x & 63) == 63) wsum[threadIdx.x >> 6] = v;
   __syncthreads();
@@ -326,8 +326,11 @@ __device__ __forceinline__ double from_next(double x) {
 // exactly one 16-lane DPP row (G = 16): shifts within the DPP rows, whose ends
 // receive 0 with no select.  HALO_WAVE: a row is exactly one wave (G = 64):
 // whole-wave shifts, 0 at the wave ends with no select.
-enum : int { HALO_SELECT = 0, HALO_DPPROW = 1, HALO_WAVE = 2 };
-inline int halo_mode(int G) { return G == 16 ? HALO_DPPROW : (G == 64 ? HALO_WAVE : HALO_SELECT); }
+// HALO_LDS: a row is two waves (G = 128): the halos by scalar LDS reads.
+enum : int { HALO_SELECT = 0, HALO_DPPROW = 1, HALO_WAVE = 2, HALO_LDS = 3 };
+inline int halo_mode(int G) {
+  return G == 16 ? HALO_DPPROW : (G == 64 ? HALO_WAVE : (G == 128 ? HALO_LDS : HALO_SELECT));
+}
 
 template <int HALO>
 __device__ __forceinline__ int halo_prev_i(int x) {
@@ -369,15 +372,26 @@ __device__ __forceinline__ T halo_next(T x, int gx, int G) {
 template <class T, int V, int HALO = HALO_SELECT>
 __device__ __forceinline__ void lds_urow(const T* row, T* dst, int gx, int G) {
   vload<T, V>(row, dst + 1);
-  dst[0] = halo_prev<HALO>(dst[V], gx);
-  dst[V + 1] = halo_next<HALO>(dst[1], gx, G);
+  if constexpr (HALO == HALO_LDS) {
+    const T l = row[gx == 0 ? 0 : -1], r = row[gx == G - 1 ? 0 : V];
+    dst[0] = gx == 0 ? T(0) : l;
+    dst[V + 1] = gx == G - 1 ? T(0) : r;
+  } else {
+    dst[0] = halo_prev<HALO>(dst[V], gx);
+    dst[V + 1] = halo_next<HALO>(dst[1], gx, G);
+  }
 }
 
 // kappa row segment: element i0-1 (zero for i0 = 0) and i0 .. i0+V-1
 template <class T, int V, int HALO = HALO_SELECT>
 __device__ __forceinline__ void lds_krow(const T* row, T* dst, int gx) {
   vload<T, V>(row, dst + 1);
-  dst[0] = halo_prev<HALO>(dst[V], gx);
+  if constexpr (HALO == HALO_LDS) {
+    const T l = row[gx == 0 ? 0 : -1];
+    dst[0] = gx == 0 ? T(0) : l;
+  } else {
+    dst[0] = halo_prev<HALO>(dst[V], gx);
+  }
 }
 
 // The 8-element sum of kappa at each of the V nodes from the four kappa row
@@ -935,10 +949,17 @@ inline size_t zlds_bytes(const ZGeom& g) {
 }
 // the staging covers every row with two vectors per thread
 // and the rings fit the 64 KiB of LDS a workgroup may take without opting in;
-// a row is at most one wave (its halos move by DPP)
+// a row is at most one wave (its halos move by DPP), or two for the fp64
+// refinement of a mixed-precision solve (zgeom_long: HALO_LDS).  That pass of
+// a 256^3 mesh was the register engine's, which reads every row from global
+// memory three times, and could not apply the update the fp32 solve owes its
+// correction: 718 us and 191 us of the separate update -> 484 us for four
+// samples (3.2 GB: 6.6 TB/s).  The other fp64 steps hold over 128 registers, one
+// such workgroup per CU, and stay with the register engine.
 template <class T, int OP = OP_PLAIN, bool PRO = false>
 inline bool zlds_ok(const ZGeom& g) {
-  return g.G >= 1 && g.G <= 64 && (g.G & (g.G - 1)) == 0 && (g.rows + 2) * g.G <= 2 * g.threads && (g.rows + 1 + 2 * ZOp<OP>::KOFF) * g.G <= 2 * g.threads &&
+  constexpr int gmax = sizeof(T) == 8 && OP == OP_ADDD ? 128 : 64;
+  return g.G >= 1 && g.G <= gmax && (g.G & (g.G - 1)) == 0 && (g.rows + 2) * g.G <= 2 * g.threads && (g.rows + 1 + 2 * ZOp<OP>::KOFF) * g.G <= 2 * g.threads &&
          zlds_bytes<T, OP, PRO>(g) <= 65536 && (!PRO || g.zc == 1 || g.zlen % 2 == 0);   // PRO: chunks start odd
 }
 
@@ -973,7 +994,7 @@ __device__ __forceinline__ void z1_form(T* u, const T* Kl, int KR, int rsh, int 
 }
 
 template <class T, int V, bool NEED_U, bool PRO, int OP, class Epi, int HALO, int NC = 0>
-__global__ void __launch_bounds__(256) k_zlds(ZGeom g, size_t stride, T h, const T* __restrict__ u,
+__global__ void __launch_bounds__(HALO == HALO_LDS ? 512 : 256) k_zlds(ZGeom g, size_t stride, T h, const T* __restrict__ u,
                                               const T* __restrict__ kap, const int* __restrict__ active,
                                               double* __restrict__ partial, uint32_t pstride, Epi epi,
                                               const T* __restrict__ xc, size_t cstride, OpArgs<T> op) {
@@ -1685,7 +1706,9 @@ __global__ void __launch_bounds__(256, (resr_min_waves<T, V, Z1, UPD>())) k_resr
 // the corrected smoothing step with its operand formed on the fly stages two
 // rows more than it computes: tall-tile geometry (see zgeom_tall)
 template <class T, bool PRO, int OP>
-inline ZGeom zlds_geom(int n, int B) { return (PRO && OP == OP_Z1) ? zgeom_tall<T>(n, B) : zgeom<T>(n, B); }
+inline ZGeom zlds_geom(int n, int B) {
+  return (PRO && OP == OP_Z1) ? zgeom_tall<T>(n, B) : (OP == OP_ADDD ? zgeom_long<T>(n, B) : zgeom<T>(n, B));
+}
 
 template <class T, bool NEED_U, bool PRO, int OP, class Epi>
 hipError_t zlaunch_lds(int n, int B, const T* u, const T* xc, const T* kap, const int* active, double* partial,
@@ -1713,6 +1736,13 @@ hipError_t zlaunch_lds(int n, int B, const T* u, const T* xc, const T* kap, cons
       k_zlds<T, V, NEED_U, PRO, OP, Epi, HALO_WAVE><<<dim3(blocks), dim3(g.threads), lds, st>>>(
           g, grid_stride(n), T(1) / T(n), u, kap, active, partial, pstride, epi, xc, cs, op);
       break;
+    case HALO_LDS:
+      if constexpr (sizeof(T) == 8 && OP == OP_ADDD) {
+        k_zlds<T, V, NEED_U, PRO, OP, Epi, HALO_LDS><<<dim3(blocks), dim3(g.threads), lds, st>>>(
+            g, grid_stride(n), T(1) / T(n), u, kap, active, partial, pstride, epi, xc, cs, op);
+        break;
+      }
+      return hipErrorInvalidValue;   // not reached: zlds_ok
     default:
       k_zlds<T, V, NEED_U, PRO, OP, Epi, HALO_SELECT><<<dim3(blocks), dim3(g.threads), lds, st>>>(
           g, grid_stride(n), T(1) / T(n), u, kap, active, partial, pstride, epi, xc, cs, op);
@@ -1725,6 +1755,10 @@ hipError_t zlaunch_lds(int n, int B, const T* u, const T* xc, const T* kap, cons
 template <class T>
 inline bool use_lds(int n, int B, int var, int bit) {
   return (var & bit) && (bit == ZVAR_LDS_PRO ? zlds_ok<T, OP_PLAIN, true>(zgeom<T>(n, B)) : zlds_ok<T>(zgeom<T>(n, B)));
+}
+template <class T>
+inline bool use_lds_addd(int n, int B, int var) {
+  return (var & ZVAR_LDS) && zlds_ok<T, OP_ADDD>(zlds_geom<T, false, OP_ADDD>(n, B));
 }
 
 template <class T, bool NEED_U, class Epi>
@@ -1751,7 +1785,7 @@ hipError_t zlaunch(int n, int B, const T* u, const T* kap, const int* active, do
 template <class T, class Epi>
 hipError_t zlaunch_addd(int n, int B, const T* u, const float* d, const T* kap, const int* active, double* partial,
                         uint32_t pstride, Epi epi, uint32_t* nparts, int var, hipStream_t st) {
-  if (use_lds<T>(n, B, var, ZVAR_LDS)) {
+  if (use_lds_addd<T>(n, B, var)) {
     OpArgs<T> op;
     op.d = d;
     return zlaunch_lds<T, true, false, OP_ADDD, Epi>(n, B, u, nullptr, kap, active, partial, pstride, epi, nparts, st,
@@ -2146,13 +2180,13 @@ hipError_t launch_refine(int n, int B, const double* kap, double bconst, const d
 }
 
 bool refine_owed_usable(int n, int B, int var) {
-  return use_lds<double>(n, B, var, ZVAR_LDS) && zlds_ok<double, OP_ADDD>(zgeom<double>(n, B));
+  return use_lds_addd<double>(n, B, var);
 }
 
 hipError_t launch_refine_owed(int n, int B, const double* kap, double bconst, const double* u, const float* d,
                               const float* p0, const float* p1, SolveState inner, double* uout, float* rin,
                               SolveState s, uint32_t* nparts, hipStream_t st, const double* bvec) {
-  if (!zlds_ok<double, OP_ADDD>(zgeom<double>(n, B))) return hipErrorInvalidValue;
+  if (!zlds_ok<double, OP_ADDD>(zlds_geom<double, false, OP_ADDD>(n, B))) return hipErrorInvalidValue;
   OpArgs<double> op;
   op.d = d;
   op.q0 = p0;

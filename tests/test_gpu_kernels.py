@@ -175,3 +175,21 @@ def test_single_kernel_vcycle_of_a_large_batch_keeps_a_samples_bits(n, deg, B):
     for a in range(0, B, 100):
         assert torch.equal(ctx.vcycle_f32(n, kap[a:a + 100].contiguous(), r[a:a + 100].contiguous()), z[a:a + 100])
     ctx.close()
+
+
+# the fp64 refinement of a 256^3 solve (rows of two waves in LDS, with and
+# without the update the fp32 solve owes): the residual it stops on is the true
+# one, b = h^3 at every interior node, up to the rounding of two fp64 evaluations
+@pytest.mark.parametrize("B,deg,direction", [(1, 1, True), (2, 2, True), (3, 1, False)])
+def test_refinement_at_256_stops_on_the_true_residual(B, deg, direction):
+    n, rtol = 256, 1e-9
+    ctx = mm.Context(_wl(n0=n, precision=1, rtol=rtol), cheb_degree=deg, arena_bytes=16 << 30)
+    if not direction:
+        ctx.set_tuning(fuse=ctx.tuning()["fuse"] & ~mm.FUSE_DIRECTION)
+    kap = ctx.field(n, ctx.draw_xi(0, 0, B))
+    u, _ = ctx.solve(n, kap)
+    b = mm.to_grid(torch.full((B, (n - 1) ** 3), n ** -3.0, dtype=torch.float64, device="cuda"), n)
+    r = b - ctx.apply(n, kap, u)
+    for s in range(B):
+        assert float(r[s].norm() / b[s].norm()) <= rtol * 1.01
+    ctx.close()
