@@ -193,3 +193,14 @@ def test_refinement_at_256_stops_on_the_true_residual(B, deg, direction):
     for s in range(B):
         assert float(r[s].norm() / b[s].norm()) <= rtol * 1.01
     ctx.close()
+
+
+# the streaming kernels run several loads ahead: spans below, at and above that
+@pytest.mark.parametrize("n", [2, 4, 16, 32, 64, 128])
+def test_domain_average_of_every_span(n):
+    ctx = mm.Context(_wl(n0=n), arena_bytes=1 << 30)
+    g = torch.Generator(device="cuda").manual_seed(n)
+    v = torch.rand((3, (n - 1) ** 3), generator=g, dtype=torch.float64, device="cuda")
+    q = np.asarray(ctx.qoi(n, mm.to_grid(v, n)).cpu())
+    assert np.allclose(q, v.sum(1).cpu().numpy() / n ** 3, rtol=1e-12, atol=0)
+    ctx.close()
