@@ -300,7 +300,9 @@ hipError_t launch_set_active(int B, SolveState s, int value, hipStream_t st);
 hipError_t launch_qoi_partial(int n, int B, int qoi, const double* u, SolveState s,
                               uint32_t* nparts, hipStream_t st, bool masked = false);
 hipError_t launch_phase_masks(int S, const int* phase, int* inner, int* trans, int* restart, int* done,
-                              hipStream_t st);
+                              int* h_phase, hipStream_t st);
+hipError_t launch_publish_done(int S, int* phase, const double* q, const int* iters, int* h_phase, double* h_q,
+                               int* h_iters, hipStream_t st);
 hipError_t launch_set_phase_list(int count, const int* slots, int* phase, int value, hipStream_t st);
 hipError_t launch_set_phase_mask(int S, const int* mask, int* phase, int value, int* zero, hipStream_t st);
 

@@ -547,9 +547,10 @@ __global__ void __launch_bounds__(kBlock) k_load(int n, size_t stride, int64_t t
   b[t] = v;
 }
 
-// per-slot masks of the serving phases
+// per-slot masks of the serving phases; the phases also to the host (h_phase,
+// pinned; may be null)
 __global__ void k_phase_masks(int S, const int* __restrict__ phase, int* __restrict__ inner, int* __restrict__ trans,
-                              int* __restrict__ restart, int* __restrict__ done) {
+                              int* __restrict__ restart, int* __restrict__ done, int* __restrict__ h_phase) {
   const int b = blockIdx.x * blockDim.x + threadIdx.x;
   if (b >= S) return;
   const int ph = phase[b];
@@ -557,6 +558,21 @@ __global__ void k_phase_masks(int S, const int* __restrict__ phase, int* __restr
   trans[b] = ph == PHASE_TRANSITION;
   restart[b] = ph == PHASE_RESTART;
   done[b] = ph == PHASE_DONE;
+  if (h_phase) h_phase[b] = ph;
+}
+
+// what a serving step hands to the host (pinned arrays): the phases, QoI and
+// iterations; the slots that are done become free
+__global__ void k_publish_done(int S, int* __restrict__ phase, const double* __restrict__ q,
+                               const int* __restrict__ iters, int* __restrict__ h_phase, double* __restrict__ h_q,
+                               int* __restrict__ h_iters) {
+  const int b = blockIdx.x * blockDim.x + threadIdx.x;
+  if (b >= S) return;
+  const int ph = phase[b];
+  h_phase[b] = ph;
+  h_q[b] = q[b];
+  h_iters[b] = iters[b];
+  if (ph == PHASE_DONE) phase[b] = PHASE_FREE;
 }
 
 // phase[slots[r]] = value for r < count
@@ -745,8 +761,14 @@ hipError_t launch_qoi_partial(int n, int B, int qoi, const double* u, SolveState
 }
 
 hipError_t launch_phase_masks(int S, const int* phase, int* inner, int* trans, int* restart, int* done,
-                              hipStream_t st) {
-  k_phase_masks<<<dim3((S + kBlock - 1) / kBlock), kBlock, 0, st>>>(S, phase, inner, trans, restart, done);
+                              int* h_phase, hipStream_t st) {
+  k_phase_masks<<<dim3((S + kBlock - 1) / kBlock), kBlock, 0, st>>>(S, phase, inner, trans, restart, done, h_phase);
+  return hipGetLastError();
+}
+
+hipError_t launch_publish_done(int S, int* phase, const double* q, const int* iters, int* h_phase, double* h_q,
+                               int* h_iters, hipStream_t st) {
+  k_publish_done<<<dim3((S + kBlock - 1) / kBlock), kBlock, 0, st>>>(S, phase, q, iters, h_phase, h_q, h_iters);
   return hipGetLastError();
 }
 
