@@ -1714,7 +1714,7 @@ template <class T, bool NEED_U, bool PRO, int OP, class Epi>
 hipError_t zlaunch_lds(int n, int B, const T* u, const T* xc, const T* kap, const int* active, double* partial,
                        uint32_t pstride, Epi epi, uint32_t* nparts, hipStream_t st, OpArgs<T> op = {}) {
   constexpr int V = ZV<T>::V;
-  const ZGeom g = zlds_geom<T, PRO, OP>(n, B);
+  const ZGeom g = zfine(zlds_geom<T, PRO, OP>(n, B), B, Epi::kReduce ? pstride : ~0u);
   if (!zlds_ok<T, OP, PRO>(g)) return hipErrorInvalidValue;
   if (nparts) *nparts = g.parts();
   const uint32_t blocks = g.blocks() * (uint32_t)B;
@@ -2248,7 +2248,7 @@ template <class T>
 hipError_t launch_residual_restrict(int n, int B, const T* kap, const T* b, const T* x, T* bc, const int* active,
                                    hipStream_t st, bool presmooth, double c2) {
   constexpr int V = ZV<T>::V;
-  const ZGeom g = resr_geom<T>(n, B);
+  const ZGeom g = zfine(resr_geom<T>(n, B), B);
   const uint32_t blocks = g.blocks() * (uint32_t)B;
   if (presmooth) {
     if (!presmooth_usable<T>(n, B)) return hipErrorInvalidValue;
@@ -2266,7 +2266,7 @@ template <class T>
 hipError_t launch_residual_restrict_update(int n, int B, const T* kap, const T* r0, T* r1, const T* q, T* bc,
                                           SolveState s, double c2, uint32_t* nparts, hipStream_t st) {
   constexpr int V = ZV<T>::V;
-  const ZGeom g = resr_geom<T>(n, B);
+  const ZGeom g = zfine(resr_geom<T>(n, B), B, s.pstride);
   if (!presmooth_usable<T>(n, B)) return hipErrorInvalidValue;
   if (nparts) *nparts = g.parts();
   ResrUpd<T> u;

@@ -204,3 +204,20 @@ def test_domain_average_of_every_span(n):
     q = np.asarray(ctx.qoi(n, mm.to_grid(v, n)).cpu())
     assert np.allclose(q, v.sum(1).cpu().numpy() / n ** 3, rtol=1e-12, atol=0)
     ctx.close()
+
+
+# a V-cycle has no sums: however its levels' planes are split (down to 8 of them
+# a workgroup at 128^3, 4 at 64^3 and 2 below for one sample), the bits are the same
+@pytest.mark.parametrize("n,B,deg", [(32, 600, 2), (64, 200, 1), (128, 12, 1), (128, 12, 3)])
+@pytest.mark.parametrize("prec", [0, 1])
+def test_vcycle_of_one_sample_has_the_bits_of_a_batch(n, B, deg, prec):
+    ctx = mm.Context(_wl(n0=n, precision=prec), cheb_degree=deg, arena_bytes=12 << 30)
+    dt = torch.float64 if prec == 0 else torch.float32
+    g = torch.Generator(device="cuda").manual_seed(n + deg)
+    kap = torch.exp(torch.randn((B, n ** 3), generator=g, dtype=torch.float64, device="cuda")).to(dt)
+    r = mm.to_grid(torch.randn((B, (n - 1) ** 3), generator=g, dtype=torch.float64, device="cuda").to(dt), n)
+    f = ctx.vcycle if prec == 0 else ctx.vcycle_f32
+    z = f(n, kap, r)
+    for s in (0, B - 1):
+        assert torch.equal(f(n, kap[s:s + 1].contiguous(), r[s:s + 1].contiguous())[0], z[s])
+    ctx.close()
