@@ -263,8 +263,7 @@ int mlmc_vcycle(mlmc_ctx* ctx, int32_t n, int64_t count, const double* kappa, co
   auto& L = ctx->sw.L64;
   L[0].kap = const_cast<double*>(kappa);
   hipStream_t st = ctx->st;
-  for (size_t l = 1; l < L.size(); ++l)
-    LAUNCH(MLMC_K_COARSEN, 0, launch_coarsen<double>(L[l - 1].n, B, L[l - 1].kap, L[l].kap, st));
+  if ((rc = coarsen_levels<double>(ctx, L, B, nullptr))) return rc;
   LAUNCH(MLMC_K_MISC, 0, launch_set_active(B, ctx->sw.outer.s, 1, st));
   double* res = nullptr;
   if ((rc = vcycle<double>(ctx, L, 0, B, r, L[0].x, L[0].xo, L[0].t, ctx->sw.outer.s.active, &res))) return rc;
@@ -288,8 +287,10 @@ int mlmc_vcycle_f32(mlmc_ctx* ctx, int32_t n, int64_t count, const float* kappa,
   float* own0 = L[0].kap;
   L[0].kap = const_cast<float*>(kappa);
   hipStream_t st = ctx->st;
-  for (size_t l = 1; l < L.size(); ++l)
-    LAUNCH(kid<float>(MLMC_K_COARSEN), 0, launch_coarsen<float>(L[l - 1].n, B, L[l - 1].kap, L[l].kap, st));
+  if ((rc = coarsen_levels<float>(ctx, L, B, nullptr))) {
+    L[0].kap = own0;
+    return rc;
+  }
   SolveState& S = ctx->sw.inner.s;
   LAUNCH(MLMC_K_MISC, 0, launch_set_active(B, S, 1, st));
   float* res = nullptr;

@@ -169,6 +169,30 @@ bool zero_step_fusable(const mlmc_ctx* ctx, const std::vector<Level<T>>& L, int 
 }
 
 template <class T>
+int coarsen_levels(mlmc_ctx* ctx, std::vector<Level<T>>& L, int B, const int* active) {
+  const double sz = sizeof(T);
+  for (size_t l = 1; l < L.size(); ++l) {
+    if (L[l - 1].n <= 32) {
+      T* kc[4];
+      int c = 0;
+      double e = elems(L[l - 1].n);
+      for (; l + c < L.size(); ++c) {
+        kc[c] = L[l + c].kap;
+        e += elems(L[l + c].n);
+      }
+      LAUNCH(kid<T>(MLMC_K_COARSEN), e * B * sz,
+             launch_coarsen_tail<T>(L[l - 1].n, B, L[l - 1].kap, kc, c, ctx->st, active));
+      return MLMC_OK;
+    }
+    LAUNCH(kid<T>(MLMC_K_COARSEN), (elems(L[l - 1].n) + elems(L[l].n)) * B * sz,
+           launch_coarsen<T>(L[l - 1].n, B, L[l - 1].kap, L[l].kap, ctx->st, active));
+  }
+  return MLMC_OK;
+}
+template int coarsen_levels<double>(mlmc_ctx*, std::vector<Level<double>>&, int, const int*);
+template int coarsen_levels<float>(mlmc_ctx*, std::vector<Level<float>>&, int, const int*);
+
+template <class T>
 int vcycle(mlmc_ctx* ctx, std::vector<Level<T>>& L, int l, int B, const T* b, T* x, T* xo, T* t,
            const int* active, T** result, SolveState* dot, uint32_t* dot_np, bool zero_done,
            const RUpdate<T>* ru) {
@@ -533,9 +557,7 @@ int solve_impl(mlmc_ctx* ctx, SolveWork& w, const double* kap, double* u, int32_
     }
     w.exec_kap = kap;
     w.exec_u = u;
-    for (size_t l = 1; l < L.size(); ++l)
-      LAUNCH(MLMC_K_COARSEN, (elems(L[l - 1].n) + elems(L[l].n)) * B * 8,
-             launch_coarsen<double>(L[l - 1].n, B, L[l - 1].kap, L[l].kap, st));
+    if (int rc = coarsen_levels<double>(ctx, L, B, nullptr)) return rc;
     LAUNCH(MLMC_K_MISC, d * 8, launch_fill_interior<double>(n, B, u, 0.0, nullptr, st));
     if (bvec)
       HIPCHK(hipMemcpyAsync(w.r, bvec, (size_t)B * S0 * sizeof(double), hipMemcpyDeviceToDevice, st));
@@ -568,9 +590,7 @@ int solve_impl(mlmc_ctx* ctx, SolveWork& w, const double* kap, double* u, int32_
     SolveState& I = w.inner.s;
     if (!kap32_ready)
       LAUNCH(MLMC_K_MISC, e * 12, (launch_convert<double, float>((size_t)B * elem_count(n), kap, L[0].kap, st)));
-    for (size_t l = 1; l < L.size(); ++l)
-      LAUNCH(kid<float>(MLMC_K_COARSEN), (elems(L[l - 1].n) + elems(L[l].n)) * B * 4,
-             launch_coarsen<float>(L[l - 1].n, B, L[l - 1].kap, L[l].kap, st));
+    if (int rc = coarsen_levels<float>(ctx, L, B, nullptr)) return rc;
     HIPCHK(hipMemsetAsync(I.iters, 0, B * sizeof(int), st));
     if (ctx->fuse & MLMC_FUSE_REFINE) {
       // Each refinement step writes u + d into the other of two fp64 buffers

@@ -467,6 +467,9 @@ template <class T>
 int vcycle(mlmc_ctx* ctx, std::vector<Level<T>>& L, int l, int B, const T* b, T* x, T* xo, T* t,
            const int* active, T** result, SolveState* dot = nullptr, uint32_t* dot_np = nullptr,
            bool zero_done = false, const RUpdate<T>* ru = nullptr);
+// the kappa of levels 1.. from level 0's (active: samples, may be null)
+template <class T>
+int coarsen_levels(mlmc_ctx* ctx, std::vector<Level<T>>& L, int B, const int* active);
 // z = M^-1 r.  When *fused_np is set on return, the partial sums of r . z
 // are already in S.partial (GMG path); otherwise the caller computes them.
 template <class T>

@@ -157,6 +157,10 @@ template <class T>
 hipError_t launch_coarsest(int B, const T* kap, const T* b, T* x, const int* active, hipStream_t st);
 template <class T>
 hipError_t launch_coarsen(int nf, int B, const T* kf, T* kc, hipStream_t st, const int* active = nullptr);
+// kc[0 .. count): the kappa of the nf/2, nf/4 .. meshes, nf <= 32
+template <class T>
+hipError_t launch_coarsen_tail(int nf, int B, const T* kf, T* const* kc, int count, hipStream_t st,
+                               const int* active = nullptr);
 template <class Ts, class Td>
 hipError_t launch_convert(size_t count, const Ts* src, Td* dst, hipStream_t st);
 template <class T>

@@ -161,8 +161,7 @@ int setup_slots(Pool& p, int c) {
   SRV_LAUNCH(launch_field(n, ctx->cfg.n_modes, c, p.xi, ctx->d_sqrtlam, ctx->d_triples, tab, ctx->K1, p.kap64,
                           L[0].kap, st, p.d_slots, ctx->cfg.precision == MLMC_PREC_MIXED_BF16KLE,
                           field_separable(ctx, c) ? ctx->d_xperm : nullptr, ctx->d_xoff));
-  for (size_t l = 1; l < L.size(); ++l)
-    SRV_LAUNCH(launch_coarsen<float>(L[l - 1].n, S, L[l - 1].kap, L[l].kap, st, p.m_new));
+  if (int rc = coarsen_levels<float>(ctx, L, S, p.m_new)) return rc;
   SRV_LAUNCH(launch_fill_interior<double>(n, S, p.u, 0.0, p.m_new, st));
   SRV_LAUNCH(launch_fill_interior<double>(n, S, p.w.r64, h * h * h, p.m_new, st));
   SolveState on = view(p.w.outer.s, p.m_new, p.phase);
