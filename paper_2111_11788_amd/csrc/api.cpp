@@ -92,6 +92,7 @@ int mlmc_create(const mlmc_config* cfg, mlmc_ctx** out) {
   if (e == hipSuccess) e = noalloc_scratch_init(&ctx->device, &ctx->scratch);
   if (e == hipSuccess) e = hipHostMalloc((void**)&ctx->h_nactive, sizeof(int), hipHostMallocDefault);
   if (e == hipSuccess) e = hipStreamSynchronize(ctx->st);
+  if (e == hipSuccess) alloc_stage(ctx);
   if (e != hipSuccess) {
     g_create_error = std::string("HIP error during create: ") + hipGetErrorString(e);
     if (ctx->h_nactive) (void)hipHostFree(ctx->h_nactive);
@@ -119,10 +120,12 @@ void mlmc_destroy(mlmc_ctx* ctx) {
     if (ln->sub) {
       (void)hipStreamSynchronize(ln->sub->st);
       (void)hipHostFree(ln->sub->h_nactive);
+      if (ln->sub->h_stage) (void)hipHostFree(ln->sub->h_stage);
       (void)hipStreamDestroy(ln->sub->st);
     }
   ctx->lanes.clear();
   if (ctx->h_nactive) (void)hipHostFree(ctx->h_nactive);
+  if (ctx->h_stage) (void)hipHostFree(ctx->h_stage);
   if (ctx->own_stream) (void)hipStreamDestroy(ctx->st);
   delete ctx;
 }

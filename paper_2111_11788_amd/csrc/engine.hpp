@@ -318,6 +318,10 @@ struct mlmc_ctx {
   int64_t k_launch[2 * MLMC_K_COUNT] = {0};   // [precision][kernel]
   double k_ms[2 * MLMC_K_COUNT] = {0}, k_bytes[2 * MLMC_K_COUNT] = {0};
   int* h_nactive = nullptr;
+  // pinned staging of what a solve or a round returns to the host (null: copied
+  // from the device to the caller's memory); larger results are not staged
+  char* h_stage = nullptr;
+  static constexpr size_t kStageBytes = 1 << 20;
   // stencil engine variant bits for fp64 / fp32 (fp32: the LDS engine also for
   // the corrected post-smoothing step, measured faster on the 64^3 batch)
   int zvar[2] = {ZVAR_LDS, ZVAR_LDS | ZVAR_LDS_PRO};
@@ -440,6 +444,7 @@ int ensure_solve_work(mlmc_ctx* ctx, int n, int B);
 // graphs captured on them: the caller is about to use the arena after the
 // persistent tables for something else.
 void drop_work(mlmc_ctx* ctx);
+void alloc_stage(mlmc_ctx* ctx);
 size_t mesh_work_bytes(const mlmc_config& c, int level, int n, int B);
 int ensure_tables(mlmc_ctx* ctx, int n, double** tab);
 // The PCG residual update r -= alpha q fused into the first kernel of the next
@@ -521,13 +526,23 @@ template <class T>
 int pcg(mlmc_ctx* ctx, std::vector<Level<T>>& L, int B, SolveState& S, T* x, T* r, T* p, T* q, double tol,
         int max_iter, int* done_iters, hipGraphExec_t* graph, T* p2 = nullptr, bool fresh = false,
         bool defer = false, T* r2 = nullptr);
+// `later` (may be null): when the outcome fits the pinned staging, the solve
+// returns with it on its way, later->pending set, and *status and iters_host
+// are written by later->take() after the stream's next synchronisation.
+struct SolveReport {
+  bool pending = false;
+  int B = 0;
+  const double* rr = nullptr;
+  const int *active = nullptr, *iters = nullptr;
+  void take(int32_t* iters_host, int* status) const;
+};
 // kap32_ready: the fp32 copy of kap is already in the fp32 hierarchy (mixed precision)
 // bvec: the right-hand side (grid layout, boundary positions 0), or NULL for f = 1
 // *status: MLMC_OK when every sample reached rtol, MLMC_E_NONFINITE when some
 // sample's residual became NaN or Inf (its solve stops there), else
 // MLMC_E_NOCONV
 int solve_impl(mlmc_ctx* ctx, SolveWork& w, const double* kap, double* u, int32_t* iters_host, int* status,
-               bool kap32_ready = false, const double* bvec = nullptr);
+               bool kap32_ready = false, const double* bvec = nullptr, SolveReport* later = nullptr);
 // xi_f, f and the load vector b of B samples (first, level) on mesh n (random forcing)
 int forcing_impl(mlmc_ctx* ctx, int n, int level, uint64_t first, int B, double* xif, double* f, double* b);
 int qoi_impl(mlmc_ctx* ctx, SolveState& S, int n, int B, const double* u, double* q);
@@ -552,7 +567,7 @@ std::vector<Task> plan_round(const mlmc_ctx* ctx, const std::vector<LevelReq>& r
 // work is done.
 int run_round(mlmc_ctx* ctx, std::vector<LevelReq>& reqs, bool record);
 // Copy the device statistics of every level into ctx->stats (n, mean, m2).
-int read_stats(mlmc_ctx* ctx);
+int read_stats(mlmc_ctx* ctx, const DevStats* rec = nullptr);
 int check_tuning(const mlmc_tuning* t, std::string& why);
 mlmc_tuning current_tuning(const mlmc_ctx* ctx);
 void apply_tuning(mlmc_ctx* ctx, const mlmc_tuning& t);

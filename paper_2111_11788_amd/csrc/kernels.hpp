@@ -305,6 +305,7 @@ hipError_t launch_qoi_partial(int n, int B, int qoi, const double* u, SolveState
                               uint32_t* nparts, hipStream_t st, bool masked = false);
 hipError_t launch_phase_masks(int S, const int* phase, int* inner, int* trans, int* restart, int* done,
                               int* h_phase, hipStream_t st);
+hipError_t launch_report(int B, SolveState s, double* h_rr, int* h_active, int* h_iters, hipStream_t st);
 hipError_t launch_publish_done(int S, int* phase, const double* q, const int* iters, int* h_phase, double* h_q,
                                int* h_iters, hipStream_t st);
 hipError_t launch_set_phase_list(int count, const int* slots, int* phase, int value, hipStream_t st);

@@ -561,6 +561,17 @@ __global__ void k_phase_masks(int S, const int* __restrict__ phase, int* __restr
   if (h_phase) h_phase[b] = ph;
 }
 
+// the outcome of a solve to the host (pinned): the samples' last residual
+// norms, which are still active, and their iterations
+__global__ void k_report(int B, SolveState st, double* __restrict__ h_rr, int* __restrict__ h_active,
+                         int* __restrict__ h_iters) {
+  const int b = blockIdx.x * blockDim.x + threadIdx.x;
+  if (b >= B) return;
+  h_rr[b] = st.rr[b];
+  h_active[b] = st.active[b];
+  h_iters[b] = st.iters[b];
+}
+
 // what a serving step hands to the host (pinned arrays): the phases, QoI and
 // iterations; the slots that are done become free
 __global__ void k_publish_done(int S, int* __restrict__ phase, const double* __restrict__ q,
@@ -763,6 +774,11 @@ hipError_t launch_qoi_partial(int n, int B, int qoi, const double* u, SolveState
 hipError_t launch_phase_masks(int S, const int* phase, int* inner, int* trans, int* restart, int* done,
                               int* h_phase, hipStream_t st) {
   k_phase_masks<<<dim3((S + kBlock - 1) / kBlock), kBlock, 0, st>>>(S, phase, inner, trans, restart, done, h_phase);
+  return hipGetLastError();
+}
+
+hipError_t launch_report(int B, SolveState s, double* h_rr, int* h_active, int* h_iters, hipStream_t st) {
+  k_report<<<dim3((B + kBlock - 1) / kBlock), kBlock, 0, st>>>(B, s, h_rr, h_active, h_iters);
   return hipGetLastError();
 }
 

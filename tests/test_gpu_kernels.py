@@ -221,3 +221,19 @@ def test_vcycle_of_one_sample_has_the_bits_of_a_batch(n, B, deg, prec):
     for s in (0, B - 1):
         assert torch.equal(f(n, kap[s:s + 1].contiguous(), r[s:s + 1].contiguous())[0], z[s])
     ctx.close()
+
+
+# results above the pinned staging of a round (and of a solve) are copied
+# straight to the caller's memory: the same numbers
+@pytest.mark.parametrize("level,count", [(0, 70000), (1, 66000)])
+def test_results_beyond_the_staging_are_the_staged_ones(level, count):
+    ctx = mm.Context(_wl(n0=4, levels=2, precision=1, rtol=1e-8), arena_bytes=6 << 30)
+    whole = ctx.sample_level(level, 0, count)
+    half = count // 2
+    parts = [ctx.sample_level(level, 0, half), ctx.sample_level(level, half, count - half)]
+    for w, a, b in zip(whole, *parts):
+        assert np.array_equal(np.asarray(w), np.concatenate([a, b]))
+    kap = ctx.field(4, ctx.draw_xi(0, 0, 70000))
+    it = ctx.solve(4, kap)[1]
+    assert np.array_equal(it[:9000], ctx.solve(4, kap[:9000].contiguous())[1])
+    ctx.close()
