@@ -263,15 +263,26 @@ hipError_t launch_reduce(int B, int op, double tol2, uint32_t nparts, SolveState
 // than the separate count takes (~2 ns each against two launches of ~4 us)
 constexpr int kCountInReduce = 4096;
 
-// Chan, Golub and LeVeque merge of the summary (nb, mb, m2b) into (n, mean, m2)
-__host__ __device__ inline void chan_merge(double& n, double& mean, double& m2, double nb, double mb, double m2b) {
+// Chan, Golub and LeVeque merge of the summary (nb, mb, m2b) into (n, mean, m2).
+// The weights depend on the counts alone, not on the values
+__host__ __device__ inline void chan_weights(double n, double nb, double& wmean, double& wm2) {
 #pragma clang fp contract(off)
-  if (nb == 0.0) return;
   const double nn = n + nb;
+  wmean = nb / nn;
+  wm2 = n * nb / nn;
+}
+__host__ __device__ inline void chan_add(double& mean, double& m2, double mb, double m2b, double wmean, double wm2) {
+#pragma clang fp contract(off)
   const double d = mb - mean;
-  mean = mean + d * (nb / nn);
-  m2 = m2 + m2b + d * d * (n * nb / nn);
-  n = nn;
+  mean = mean + d * wmean;
+  m2 = m2 + m2b + d * d * wm2;
+}
+__host__ __device__ inline void chan_merge(double& n, double& mean, double& m2, double nb, double mb, double m2b) {
+  if (nb == 0.0) return;
+  double w1, w2;
+  chan_weights(n, nb, w1, w2);
+  chan_add(mean, m2, mb, m2b, w1, w2);
+  n = n + nb;
 }
 
 // Level statistics fold (one workgroup per job): Y = qf - qc (qc may be null:
