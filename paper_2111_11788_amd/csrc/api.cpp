@@ -92,7 +92,6 @@ int mlmc_create(const mlmc_config* cfg, mlmc_ctx** out) {
   if (e == hipSuccess) e = noalloc_scratch_init(&ctx->device, &ctx->scratch);
   if (e == hipSuccess) e = hipHostMalloc((void**)&ctx->h_nactive, sizeof(int), hipHostMallocDefault);
   if (e == hipSuccess) e = hipStreamSynchronize(ctx->st);
-  if (e == hipSuccess) alloc_stage(ctx);
   if (e != hipSuccess) {
     g_create_error = std::string("HIP error during create: ") + hipGetErrorString(e);
     if (ctx->h_nactive) (void)hipHostFree(ctx->h_nactive);

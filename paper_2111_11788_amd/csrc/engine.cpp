@@ -71,12 +71,16 @@ void drop_work(mlmc_ctx* ctx) {
   }
 }
 
-// The pinned staging; without it results are copied one by one
-void alloc_stage(mlmc_ctx* ctx) {
-  if (hipHostMalloc((void**)&ctx->h_stage, mlmc_ctx::kStageBytes, hipHostMallocDefault) != hipSuccess) {
-    (void)hipGetLastError();
-    ctx->h_stage = nullptr;
+// The pinned staging; without it (null) results are copied one by one
+char* stage_of(mlmc_ctx* ctx) {
+  if (!ctx->stage_tried) {
+    ctx->stage_tried = true;
+    if (hipHostMalloc((void**)&ctx->h_stage, mlmc_ctx::kStageBytes, hipHostMallocDefault) != hipSuccess) {
+      (void)hipGetLastError();
+      ctx->h_stage = nullptr;
+    }
   }
+  return ctx->h_stage;
 }
 
 // Carve a solve work space for (n, B) unless the cached one matches.
@@ -694,7 +698,7 @@ int solve_impl(mlmc_ctx* ctx, SolveWork& w, const double* kap, double* u, int32_
   rep.B = B;
   std::vector<double> rr;
   std::vector<int> act, its;
-  if (ctx->h_stage && (size_t)B * 16 <= mlmc_ctx::kStageBytes) {
+  if ((size_t)B * 16 <= mlmc_ctx::kStageBytes && stage_of(ctx)) {
     // one launch writes all three arrays to pinned memory; copies to pageable
     // memory are ~25 us each, one after another
     double* hr = reinterpret_cast<double*>(ctx->h_stage);
@@ -902,7 +906,6 @@ int ensure_lanes(mlmc_ctx* ctx, int K) {
         (void)hipStreamDestroy(sub->st);
         FAIL(MLMC_E_DEVICE, "cannot allocate a lane counter");
       }
-      alloc_stage(sub.get());
       ln->sub = std::move(sub);
     }
     ctx->lanes.push_back(std::move(ln));
@@ -1166,7 +1169,7 @@ int run_round(mlmc_ctx* ctx, std::vector<LevelReq>& reqs, bool record) {
   // level); staged in pinned memory where they fit, with one synchronisation
   // (each copy to pageable memory is one, of ~25 us: one pair of samples of
   // 16^3 / 8^3 433 -> 308 us, 13000 samples of 8^3 944 -> 833 us)
-  const bool staged = ctx->h_stage && qbytes + c.levels * sizeof(DevStats) <= mlmc_ctx::kStageBytes;
+  const bool staged = qbytes + c.levels * sizeof(DevStats) <= mlmc_ctx::kStageBytes && stage_of(ctx);
   const double* hqf = reinterpret_cast<const double*>(ctx->h_stage);
   const double* hqc = hqf + (dqc - dqf);
   DevStats* hstats = reinterpret_cast<DevStats*>(ctx->h_stage + qbytes);

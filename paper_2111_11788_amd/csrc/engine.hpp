@@ -318,10 +318,12 @@ struct mlmc_ctx {
   int64_t k_launch[2 * MLMC_K_COUNT] = {0};   // [precision][kernel]
   double k_ms[2 * MLMC_K_COUNT] = {0}, k_bytes[2 * MLMC_K_COUNT] = {0};
   int* h_nactive = nullptr;
-  // pinned staging of what a solve or a round returns to the host (null: copied
-  // from the device to the caller's memory); larger results are not staged
+  // pinned staging of what a solve or a round returns to the host, taken by the
+  // first (null: copied from the device to the caller's memory); larger results
+  // are not staged
   char* h_stage = nullptr;
-  static constexpr size_t kStageBytes = 1 << 20;
+  static constexpr size_t kStageBytes = 1 << 18;
+  bool stage_tried = false;
   // stencil engine variant bits for fp64 / fp32 (fp32: the LDS engine also for
   // the corrected post-smoothing step, measured faster on the 64^3 batch)
   int zvar[2] = {ZVAR_LDS, ZVAR_LDS | ZVAR_LDS_PRO};
@@ -444,7 +446,7 @@ int ensure_solve_work(mlmc_ctx* ctx, int n, int B);
 // graphs captured on them: the caller is about to use the arena after the
 // persistent tables for something else.
 void drop_work(mlmc_ctx* ctx);
-void alloc_stage(mlmc_ctx* ctx);
+char* stage_of(mlmc_ctx* ctx);
 size_t mesh_work_bytes(const mlmc_config& c, int level, int n, int B);
 int ensure_tables(mlmc_ctx* ctx, int n, double** tab);
 // The PCG residual update r -= alpha q fused into the first kernel of the next

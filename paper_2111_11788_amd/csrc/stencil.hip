@@ -2036,14 +2036,14 @@ template <class T>
 __global__ void __launch_bounds__(512) k_coarsen_tail(int nf, const T* __restrict__ kf, CoarseLevels<T> lv,
                                                       const int* __restrict__ active) {
   typedef typename Vec<T, 2>::type t2;
-  __shared__ __align__(16) T bufs[2][16 * 16 * 16];
+  __shared__ __align__(16) T buf0[16 * 16 * 16], buf1[8 * 8 * 8];
   const uint32_t b = blockIdx.x;
   if (active && !active[b]) return;   // uniform over the workgroup
   const T* src = kf + (size_t)b * nf * nf * nf;
   for (int l = 0; l < lv.count; ++l, nf /= 2) {
     const int nc = nf / 2, lg = __builtin_ctz((unsigned)nc), f2 = nf * nf;
     T* out = lv.kap[l] + (size_t)b * nc * nc * nc;
-    T* keep = bufs[l & 1];
+    T* keep = l & 1 ? buf1 : buf0;
     for (int E = (int)threadIdx.x; E < nc * nc * nc; E += 512) {
       const int EX = E & (nc - 1), EY = (E >> lg) & (nc - 1), EZ = E >> (2 * lg);
       const T* f = src + 2 * EX + nf * 2 * EY + f2 * 2 * EZ;
