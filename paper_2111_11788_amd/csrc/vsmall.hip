@@ -6,8 +6,9 @@
 // the place of ~7 per level and ~10 per iteration, and no vector leaves the CU.
 //
 // A thread owns four consecutive nodes of a row (16^3: 960 of 1024 threads,
-// 8^3: 112 of 128, 4^3: 12 of one wave).  Its right-hand side, iterates,
-// inverse diagonal and Krylov vectors stay in its registers on every level;
+// 8^3: 112 of 128, 4^3: 12 of one wave), one on the coarser levels (small_v).
+// Its right-hand side, iterates, inverse diagonal and Krylov vectors stay in its
+// registers on every level;
 // LDS holds, per level, two copies of the vector the neighbours read (boundary
 // positions 0) and kappa.  A stencil takes nine row reads of four values and
 // the row halos from the neighbouring lanes, instead of 29 scalar reads a
@@ -72,37 +73,49 @@ __device__ __forceinline__ double lane_next(double x) {
   return __longlong_as_double(((long long)lane_next((int)(v >> 32)) << 32) | (unsigned)lane_next((int)v));
 }
 
-// The thread's four nodes on the n^3 mesh (n >= 4): lanes of a row are
+// N consecutive values
+template <int N, class T>
+__device__ __forceinline__ void ldv(const T* p, T* d) {
+  if constexpr (N == 1) d[0] = *p;
+  else ld4(p, d);
+}
+template <int N, class T>
+__device__ __forceinline__ void stv(T* p, const T* d) {
+  if constexpr (N == 1) *p = d[0];
+  else st4(p, d);
+}
+
+// The thread's V = 4 or 1 nodes on the n^3 mesh (n >= 4): lanes of a row are
 // consecutive, so the row halos move between lanes.
-template <int n>
+template <int n, int V = 4>
 struct Own {
-  static constexpr int G = n / 4, NV = (n - 1) * n * G;   // vectors of planes 1 .. n-1
+  static constexpr int G = n / V, NV = (n - 1) * n * G;   // vectors of planes 1 .. n-1
   int gx, pos;
   bool has;       // row j >= 1: holds interior nodes
   __device__ Own() {
     const int v = (int)threadIdx.x;
     gx = v & (G - 1);
-    pos = n * n + 4 * v;
+    pos = n * n + V * v;
     has = v < NV && ((v / G) & (n - 1)) != 0;
   }
-  // columns c = 0 .. 5: nodes i0-1 .. i0+4 of a node row, 0 beyond the mesh
+  // columns c = 0 .. V+1: nodes i0-1 .. i0+V of a node row, 0 beyond the mesh
   template <class T>
-  __device__ void urow(const T* row, T (&q)[6]) const {
-    ld4(row, q + 1);
+  __device__ void urow(const T* row, T (&q)[V + 2]) const {
+    ldv<V>(row, q + 1);
     if constexpr (G > 1) {
-      const T l = lane_prev(q[4]), r = lane_next(q[1]);
+      const T l = lane_prev(q[V]), r = lane_next(q[1]);
       q[0] = gx == 0 ? T(0) : l;
-      q[5] = gx == G - 1 ? T(0) : r;
+      q[V + 1] = gx == G - 1 ? T(0) : r;
     } else {
-      q[0] = q[5] = T(0);
+      q[0] = q[V + 1] = T(0);
     }
   }
-  // columns 0 .. 4: elements i0-1 .. i0+3 of an element row
+  // columns 0 .. V: elements i0-1 .. i0+V-1 of an element row
   template <class T>
-  __device__ void krow(const T* row, T (&q)[5]) const {
-    ld4(row, q + 1);
+  __device__ void krow(const T* row, T (&q)[V + 1]) const {
+    ldv<V>(row, q + 1);
     if constexpr (G > 1) {
-      const T l = lane_prev(q[4]);
+      const T l = lane_prev(q[V]);
       q[0] = gx == 0 ? T(0) : l;
     } else {
       q[0] = T(0);
@@ -111,18 +124,18 @@ struct Own {
 };
 
 // the 8-element kappa sums of the thread's nodes, one element after another
-template <int n, class T>
-__device__ __forceinline__ void ksum4(const Own<n>& o, const T* kap, T (&ks)[4]) {
+template <int n, int V, class T>
+__device__ __forceinline__ void ksum4(const Own<n, V>& o, const T* kap, T (&ks)[V]) {
 #pragma unroll
-  for (int v = 0; v < 4; ++v) ks[v] = T(0);
+  for (int v = 0; v < V; ++v) ks[v] = T(0);
 #pragma unroll
   for (int dz = 0; dz < 2; ++dz)
 #pragma unroll
     for (int dy = 0; dy < 2; ++dy) {
-      T K[5];
+      T K[V + 1];
       o.krow(kap + o.pos - n - n * n + n * dy + n * n * dz, K);
 #pragma unroll
-      for (int v = 0; v < 4; ++v) {
+      for (int v = 0; v < V; ++v) {
         ks[v] += K[v];
         ks[v] += K[v + 1];
       }
@@ -131,25 +144,25 @@ __device__ __forceinline__ void ksum4(const Own<n>& o, const T* kap, T (&ks)[4])
 
 // A u at the thread's nodes (u in LDS, grid layout), element by element: kappa
 // times the sum of its three edge diagonals and its corner
-template <int n, class T>
-__device__ __forceinline__ void q1v(const Own<n>& o, const T* u, const T* kap, T (&au)[4]) {
+template <int n, int V, class T>
+__device__ __forceinline__ void q1v(const Own<n, V>& o, const T* u, const T* kap, T (&au)[V]) {
   constexpr int n2 = n * n;
   const T* up = u + o.pos;
   const T* kp = kap + o.pos - n - n2;
-  T f[4], ks[4], M[3][6];   // M: the rows of the node's own plane
+  T f[V], ks[V], M[3][V + 2];   // M: the rows of the node's own plane
 #pragma unroll
   for (int r = 0; r < 3; ++r) o.urow(up + n * (r - 1), M[r]);
 #pragma unroll
-  for (int v = 0; v < 4; ++v) f[v] = ks[v] = T(0);
+  for (int v = 0; v < V; ++v) f[v] = ks[v] = T(0);
 #pragma unroll
   for (int sz = 0; sz < 2; ++sz) {
-    T K[2][5], Q[3][6];
+    T K[2][V + 1], Q[3][V + 2];
     o.krow(kp + n2 * sz, K[0]);
     o.krow(kp + n2 * sz + n, K[1]);
 #pragma unroll
     for (int r = 0; r < 3; ++r) o.urow(up + n2 * (2 * sz - 1) + n * (r - 1), Q[r]);
 #pragma unroll
-    for (int v = 0; v < 4; ++v)
+    for (int v = 0; v < V; ++v)
 #pragma unroll
       for (int sy = 0; sy < 2; ++sy)
 #pragma unroll
@@ -162,7 +175,7 @@ __device__ __forceinline__ void q1v(const Own<n>& o, const T* u, const T* kap, T
   }
   const T h = T(1) / T(n);
 #pragma unroll
-  for (int v = 0; v < 4; ++v) {
+  for (int v = 0; v < V; ++v) {
     const T a = h * (ks[v] * M[1][v + 1] * (T(1) / T(3)) - f[v] * (T(1) / T(12)));
     au[v] = (v > 0 || o.gx != 0) ? a : T(0);
   }
@@ -171,26 +184,26 @@ __device__ __forceinline__ void q1v(const Own<n>& o, const T* u, const T* kap, T
 // As q1v, with the kappa sums as a result and one element row at a time: about 35
 // values live (the rows of the own plane are read twice), for a kernel held to 64
 // registers
-template <int n, class T>
-__device__ __forceinline__ void q1v_lean(const Own<n>& o, const T* u, const T* kap, T (&au)[4], T (&ks)[4]) {
+template <int n, int V, class T>
+__device__ __forceinline__ void q1v_lean(const Own<n, V>& o, const T* u, const T* kap, T (&au)[V], T (&ks)[V]) {
   constexpr int n2 = n * n;
   const T* up = u + o.pos;
   const T* kp = kap + o.pos - n - n2;
-  T f[4];
+  T f[V];
 #pragma unroll
-  for (int v = 0; v < 4; ++v) f[v] = ks[v] = T(0);
+  for (int v = 0; v < V; ++v) f[v] = ks[v] = T(0);
 #pragma unroll
   for (int sz = 0; sz < 2; ++sz) {
-    T Q1[6];
+    T Q1[V + 2];
     o.urow(up + n2 * (2 * sz - 1), Q1);
 #pragma unroll
     for (int sy = 0; sy < 2; ++sy) {
-      T K[5], M[6], Q[6];
+      T K[V + 1], M[V + 2], Q[V + 2];
       o.krow(kp + n2 * sz + n * sy, K);
       o.urow(up + n * (2 * sy - 1), M);
       o.urow(up + n2 * (2 * sz - 1) + n * (2 * sy - 1), Q);
 #pragma unroll
-      for (int v = 0; v < 4; ++v)
+      for (int v = 0; v < V; ++v)
 #pragma unroll
         for (int sx = 0; sx < 2; ++sx) {
           const T kv = K[v + sx];
@@ -201,11 +214,11 @@ __device__ __forceinline__ void q1v_lean(const Own<n>& o, const T* u, const T* k
       __builtin_amdgcn_sched_barrier(0);
     }
   }
-  T uc[4];
-  ld4(up, uc);
+  T uc[V];
+  ldv<V>(up, uc);
   const T h = T(1) / T(n);
 #pragma unroll
-  for (int v = 0; v < 4; ++v) {
+  for (int v = 0; v < V; ++v) {
     const T a = h * (ks[v] * uc[v] * (T(1) / T(3)) - f[v] * (T(1) / T(12)));
     au[v] = (v > 0 || o.gx != 0) ? a : T(0);
   }
@@ -314,6 +327,21 @@ __device__ __forceinline__ double keep_diag(double d) { return 1.0 / d; }
 __device__ __forceinline__ float scale_diag(float x, float kept) { return x / kept; }
 __device__ __forceinline__ double scale_diag(double x, double kept) { return x * kept; }
 
+// threads of a workgroup: one per vector of the finest mesh
+template <int NL>
+constexpr int small_threads() { return NL == 4 ? 1024 : (NL == 3 ? 128 : 64); }
+
+// nodes per thread on level L: One (below the finest mesh, where the workgroup
+// has a thread per node), else four.  Those levels are chains of short phases, and one
+// node's stencil is shorter than four's: 13000 samples of 8^3 816 -> 798 us, 32 pairs
+// of 32^3 / 16^3 945 -> 927, 1024 of 64^3 39.1 -> 38.9 ms.  Not in the whole solve of 16^3,
+// which spills 38 registers then in place of 27 (one pair with 8^3: 307 against 327 us)
+template <int NL, int L, bool One>
+constexpr int small_v() {
+  constexpr int n = (1 << NL) >> L;
+  return One && L > 0 && n * n * (n - 1) <= small_threads<NL>() ? 1 : 4;
+}
+
 // LDS of the levels of a V-cycle from 2^NL down: two vectors and kappa each
 template <class T, int NL>
 struct Levels {
@@ -345,65 +373,67 @@ struct Nodes {
 };
 
 // the diagonals of the levels (kappa in LDS)
-template <class T, int NL, int L>
+template <class T, int NL, int L, bool One = true>
 __device__ __forceinline__ void form_diag(const Levels<T, NL>& lv, Nodes<T, NL>& nd) {
   constexpr int n = (1 << NL) >> L;
   if constexpr (n > 2) {
-    const Own<n> o;
+    constexpr int V = small_v<NL, L, One>();
+    const Own<n, V> o;
 #pragma unroll
-    for (int v = 0; v < 4; ++v) nd.dg[L][v] = T(1);
+    for (int v = 0; v < V; ++v) nd.dg[L][v] = T(1);
     if (o.has) {
-      T ks[4];
+      T ks[V];
       ksum4<n>(o, lv.K[L], ks);
 #pragma unroll
-      for (int v = 0; v < 4; ++v) nd.dg[L][v] = keep_diag(diag_of<n>(ks[v]));
+      for (int v = 0; v < V; ++v) nd.dg[L][v] = keep_diag(diag_of<n>(ks[v]));
     }
-    form_diag<T, NL, L + 1>(lv, nd);
+    form_diag<T, NL, L + 1, One>(lv, nd);
   }
 }
 
 // One V-cycle from level L: nd.b[L] the right-hand side, nd.x[L] the result (and
 // an LDS copy in lv.x(L, return value) for L > 0).  Called by every thread.
 // Lean: few registers, the diagonals formed where they are used.
-template <class T, int NL, int L, bool Lean = false>
+template <class T, int NL, int L, bool Lean = false, bool One = true>
 __device__ int vcycle_small(const SmallArgs& a, const Levels<T, NL>& lv, Nodes<T, NL>& nd) {
   constexpr int n = (1 << NL) >> L;
-  const Own<n> o;
+  constexpr int V = small_v<NL, L, One>();
+  const Own<n, V> o;
   T (&b)[4] = nd.b[L];
   T (&x)[4] = nd.x[L];
   T (&dg)[4] = nd.dg[L];
   const T* kap = lv.K[L];
   int c = 0;
-  T xo[4];
+  T xo[V];
   // pre-smoothing from 0
 #pragma unroll
-  for (int v = 0; v < 4; ++v) x[v] = T(0);
+  for (int v = 0; v < V; ++v) x[v] = T(0);
   if (o.has) {
     if constexpr (Lean) {
-      T ks[4];
+      T ks[V];
       ksum4<n>(o, kap, ks);
 #pragma unroll
-      for (int v = 0; v < 4; ++v) dg[v] = diag_of<n>(ks[v]);
+      for (int v = 0; v < V; ++v) dg[v] = diag_of<n>(ks[v]);
     }
 #pragma unroll
-    for (int v = 0; v < 4; ++v) x[v] = (v > 0 || o.gx != 0) ? scale_diag(T(a.c2[0]) * b[v], dg[v]) : T(0);
-    st4(lv.x(L, c) + o.pos, x);
+    for (int v = 0; v < V; ++v) x[v] = (v > 0 || o.gx != 0) ? scale_diag(T(a.c2[0]) * b[v], dg[v]) : T(0);
+    stv<V>(lv.x(L, c) + o.pos, x);
   }
   __syncthreads();
   // one smoothing step: x <- x + c1 (x - xo) + c2 D^-1 (b - A x)
   auto smooth = [&](T c1, T c2, bool use_xo) {
     if (o.has) {
-      T au[4];
+      T au[V];
       if constexpr (Lean) {
-        T ks[4];
+        T ks[V];
         q1v_lean<n>(o, lv.x(L, c), kap, au, ks);
 #pragma unroll
-        for (int v = 0; v < 4; ++v) dg[v] = diag_of<n>(ks[v]);
+        for (int v = 0; v < V; ++v) dg[v] = diag_of<n>(ks[v]);
       } else {
         q1v<n>(o, lv.x(L, c), kap, au);
       }
 #pragma unroll
-      for (int v = 0; v < 4; ++v) {
+      for (int v = 0; v < V; ++v) {
         const T prev = use_xo ? x[v] - xo[v] : x[v];
         const T xn = x[v] + c1 * prev + scale_diag(c2 * (b[v] - au[v]), dg[v]);
         xo[v] = x[v];
@@ -413,7 +443,7 @@ __device__ int vcycle_small(const SmallArgs& a, const Levels<T, NL>& lv, Nodes<T
   };
   auto publish = [&] {
     c ^= 1;
-    if (o.has) st4(lv.x(L, c) + o.pos, x);
+    if (o.has) stv<V>(lv.x(L, c) + o.pos, x);
     __syncthreads();
   };
   for (int st = 1; st < a.degree; ++st) {
@@ -422,16 +452,16 @@ __device__ int vcycle_small(const SmallArgs& a, const Levels<T, NL>& lv, Nodes<T
   }
   // the residual into the other copy
   if (o.has) {
-    T t[4];
+    T t[V];
     if constexpr (Lean) {
-      T ks[4];
+      T ks[V];
       q1v_lean<n>(o, lv.x(L, c), kap, t, ks);
     } else {
       q1v<n>(o, lv.x(L, c), kap, t);
     }
 #pragma unroll
-    for (int v = 0; v < 4; ++v) t[v] = b[v] - t[v];
-    st4(lv.x(L, c ^ 1) + o.pos, t);
+    for (int v = 0; v < V; ++v) t[v] = b[v] - t[v];
+    stv<V>(lv.x(L, c ^ 1) + o.pos, t);
   }
   __syncthreads();
   const T* t = lv.x(L, c ^ 1);
@@ -439,34 +469,37 @@ __device__ int vcycle_small(const SmallArgs& a, const Levels<T, NL>& lv, Nodes<T
   const T* xc;
   if constexpr (nc > 2) {
     // full weighting: coarse node (I, J, K) from fine (2I + dx, 2J + dy, 2K + dz)
-    const Own<nc> oc;
+    constexpr int VC = small_v<NL, L + 1, One>();
+    const Own<nc, VC> oc;
     T (&bc)[4] = nd.b[L + 1];
 #pragma unroll
-    for (int v = 0; v < 4; ++v) bc[v] = T(0);
+    for (int v = 0; v < VC; ++v) bc[v] = T(0);
     if (oc.has) {
       constexpr int lc = nc == 4 ? 2 : 3;
       const int I0 = oc.pos & (nc - 1), J = (oc.pos >> lc) & (nc - 1), K = oc.pos >> (2 * lc);
       const T* tp = t + 2 * I0 + n * 2 * J + n2 * 2 * K;
 #pragma unroll
       for (int dz = -1; dz <= 1; ++dz) {
-        T az[4] = {T(0), T(0), T(0), T(0)};
+        T az[VC];
+#pragma unroll
+        for (int v = 0; v < VC; ++v) az[v] = T(0);
 #pragma unroll
         for (int dy = -1; dy <= 1; ++dy) {
           const T* row = tp + n * dy + n2 * dz;
-          T f[9];
+          T f[2 * VC + 1];
           f[0] = row[-1];   // of use where I0 > 0 only
-          ld4(row, f + 1);
-          ld4(row + 4, f + 5);
+          ldv<VC>(row, f + 1);
+          ldv<VC>(row + VC, f + 1 + VC);
 #pragma unroll
-          for (int v = 0; v < 4; ++v)
+          for (int v = 0; v < VC; ++v)
             az[v] += (dy == 0 ? T(1) : T(0.5)) * (T(0.5) * (f[2 * v] + f[2 * v + 2]) + f[2 * v + 1]);
         }
 #pragma unroll
-        for (int v = 0; v < 4; ++v) bc[v] += (dz == 0 ? T(1) : T(0.5)) * az[v];
+        for (int v = 0; v < VC; ++v) bc[v] += (dz == 0 ? T(1) : T(0.5)) * az[v];
       }
       if (oc.gx == 0) bc[0] = T(0);
     }
-    const int cc = vcycle_small<T, NL, L + 1, Lean>(a, lv, nd);
+    const int cc = vcycle_small<T, NL, L + 1, Lean, One>(a, lv, nd);
     xc = lv.x(L + 1, cc);
   } else {
     // 2^3: one unknown, A_11 = (h / 3) sum of the 8 kappa, h = 1/2
@@ -493,24 +526,30 @@ __device__ int vcycle_small(const SmallArgs& a, const Levels<T, NL>& lv, Nodes<T
   if (o.has) {
     constexpr int lf = n == 16 ? 4 : (n == 8 ? 3 : 2), c2n = nc * nc;
     const int j = (o.pos >> lf) & (n - 1), k = o.pos >> (2 * lf);
-    T pl[2][4];
+    T pl[2][V];
 #pragma unroll
     for (int z = 0; z < 2; ++z) {
-      T rw[2][4];
+      T rw[2][V];
 #pragma unroll
       for (int y = 0; y < 2; ++y) {
-        const T* row = xc + 2 * o.gx + nc * ((j + y) >> 1) + c2n * ((k + z) >> 1);
-        const T p0 = row[0], p1 = row[1], p2 = row[2];
-        rw[y][0] = p0;
-        rw[y][1] = T(0.5) * (p0 + p1);
-        rw[y][2] = p1;
-        rw[y][3] = T(0.5) * (p1 + p2);
+        if constexpr (V == 4) {
+          const T* row = xc + 2 * o.gx + nc * ((j + y) >> 1) + c2n * ((k + z) >> 1);
+          const T p0 = row[0], p1 = row[1], p2 = row[2];
+          rw[y][0] = p0;
+          rw[y][1] = T(0.5) * (p0 + p1);
+          rw[y][2] = p1;
+          rw[y][3] = T(0.5) * (p1 + p2);
+        } else {
+          const T* row = xc + (o.gx >> 1) + nc * ((j + y) >> 1) + c2n * ((k + z) >> 1);
+          const T p0 = row[0], p1 = row[1];
+          rw[y][0] = (o.gx & 1) ? T(0.5) * (p0 + p1) : p0;
+        }
       }
 #pragma unroll
-      for (int v = 0; v < 4; ++v) pl[z][v] = (j & 1) ? T(0.5) * (rw[0][v] + rw[1][v]) : rw[0][v];
+      for (int v = 0; v < V; ++v) pl[z][v] = (j & 1) ? T(0.5) * (rw[0][v] + rw[1][v]) : rw[0][v];
     }
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
+    for (int v = 0; v < V; ++v) {
       const T e = (k & 1) ? T(0.5) * (pl[0][v] + pl[1][v]) : pl[0][v];
       x[v] += (v > 0 || o.gx != 0) ? e : T(0);
     }
@@ -522,10 +561,6 @@ __device__ int vcycle_small(const SmallArgs& a, const Levels<T, NL>& lv, Nodes<T
   }
   return c;
 }
-
-// threads of a workgroup: one per vector of the finest mesh
-template <int NL>
-constexpr int small_threads() { return NL == 4 ? 1024 : (NL == 3 ? 128 : 64); }
 
 // Lean: two workgroups of 16^3 per CU (64 registers, 60 KB of LDS each)
 template <class T, int NL, bool Lean>
@@ -653,7 +688,7 @@ __device__ void pcg_small(const SmallArgs& a, const Levels<T, NL>& lv, Nodes<T, 
   bool first = true;
   while (total < max_iter) {
     if (GMG) {
-      vcycle_small<T, NL, 0>(a, lv, nd);
+      vcycle_small<T, NL, 0, false, NL != 4>(a, lv, nd);
     } else {
 #pragma unroll
       for (int v = 0; v < 4; ++v) z[v] = scale_diag(r[v], nd.dg[0][v]);
@@ -727,7 +762,7 @@ __global__ void __launch_bounds__(small_threads<NL>(), NL == 2 ? 1 : 4) k_solve_
   __syncthreads();
   coarsen_lds<float, NL>(lv);
   Nodes<float, NL> nd;
-  form_diag<float, NL, 0>(lv, nd);
+  form_diag<float, NL, 0, NL != 4>(lv, nd);
   const double* bg = bvec ? bvec + (size_t)smp * a.v.gstride : nullptr;
   // the right-hand side at the thread's nodes, 0 on the boundary
   auto rhs = [&](double (&b)[4]) {
