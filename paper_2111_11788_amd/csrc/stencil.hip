@@ -924,6 +924,17 @@ struct OpArgs {
   const double* beta = nullptr;   // OP_DIR
 };
 
+// OP_DIR in fp32: how z + beta p_old is rounded.  Once (fma), except on the two
+// rows beyond the tile, where planes 1 and 2 of every kDirUnit planes have the
+// product and the sum rounded each (plane 1 only for planes 1 and 2: plane 0
+// reads it as an fma).  Either would be as accurate, but the rounding of the
+// first inner fp32 solve is what Y = Q_l - Q_{l-1} of fine meshes cancels least,
+// so it stays as the results of these solves have always had it: one fma
+// everywhere moves Y of a 128^3 / 64^3 pair by up to 1e-8 of it.  Units are counted
+// from the mesh's first plane, not from a chunk's, so a sample's bits do not
+// depend on how its planes are split (chunks are multiples of 4 planes).
+constexpr int kDirUnit = 16;
+
 template <int OP> struct ZOp {
   static constexpr int KOFF = OP == OP_Z1 ? 1 : 0;   // extra kappa rows on each side
   static constexpr int KP = OP == OP_Z1 ? 4 : 2;     // kappa ring planes
@@ -1142,7 +1153,9 @@ __global__ void __launch_bounds__(HALO == HALO_LDS ? 512 : 256) k_zlds(ZGeom g, 
   // the ring), then PRO adds the correction from the coarse window fetched
   // with it.  Done before the barrier that precedes put_u, so it overlaps the
   // other waves' stencil work instead of stalling the workgroup.
-  auto prep_u = [&](int kk) {
+  constexpr bool UNITS = DIR && sizeof(T) == 4;   // see kDirUnit
+  vt pedge{};   // UNITS: the second vector of the first plane of a unit, as planes 1 and 2 of it read it
+  auto prep_u = [&](int kk, bool first) {
 #pragma unroll
     for (int m = 0; m < 2; ++m) {
       const int v = uv(m);
@@ -1194,11 +1207,20 @@ __global__ void __launch_bounds__(HALO == HALO_LDS ? 512 : 256) k_zlds(ZGeom g, 
 #pragma unroll
           for (int t = 0; t < V; ++t) pu[m][t] += (T)dd[t];
         }
-        // explicit fused multiply-adds: every copy of this code rounds the same,
-        // so a value does not depend on where a chunk of planes starts
-        if (DIR && dir_prev)
+        // the rounding is written out, so that it is the same in every copy of
+        // this code; a thread's second vector is of a row beyond the tile
+        if (DIR && dir_prev) {
+#pragma clang fp contract(off)
+          const vt po = pp[DIR ? m : 0];
+          const int up = (kk - 1) % kDirUnit;
+          if (UNITS && m == 1 && (up == 1 || (up == 0 && first))) {
+            pu[m] = pu[m] + dbeta * po;
+          } else {
+            if (UNITS && m == 1 && up == 0) pedge = pu[m] + dbeta * po;
 #pragma unroll
-          for (int t = 0; t < V; ++t) pu[m][t] = fma(dbeta, pp[DIR ? m : 0][t], pu[m][t]);
+            for (int t = 0; t < V; ++t) pu[m][t] = fma(dbeta, po[t], pu[m][t]);
+          }
+        }
       }
     }
   };
@@ -1210,8 +1232,13 @@ __global__ void __launch_bounds__(HALO == HALO_LDS ? 512 : 256) k_zlds(ZGeom g, 
       if (v < UR * G && j0 - 1 + r <= n) *reinterpret_cast<vt*>(Ul + ((slot * UR + r) << rsh) + c * V) = pu[m];
     }
   };
+  auto put_edge = [&](int slot) {
+    const int v = uv(1);
+    const int r = v >> gsh, c = v & (G - 1);
+    if (v < UR * G && j0 - 1 + r <= n) *reinterpret_cast<vt*>(Ul + ((slot * UR + r) << rsh) + c * V) = pedge;
+  };
   auto store_u = [&](int slot, int kk) {
-    prep_u(kk);
+    prep_u(kk, true);
     put_u(slot);
   };
   auto fetch_k = [&](int ez) {
@@ -1327,10 +1354,12 @@ __global__ void __launch_bounds__(HALO == HALO_LDS ? 512 : 256) k_zlds(ZGeom g, 
       if (k + 1 < k1) {
         // u plane k+2 (OP_Z1: from kappa planes k+1, k+2, stored in earlier
         // steps; kappa plane k+3 takes the slot of plane k-1 below)
-        if (NEED_U && k + 2 <= k1) prep_u(k + 2);
+        if (NEED_U && k + 2 <= k1) prep_u(k + 2, false);
         // every thread is done with u plane k-1 and kappa plane k-1
         __syncthreads();
         if (NEED_U && k + 2 <= k1) put_u(sm);   // plane k+2 takes the slot of plane k-1
+        if constexpr (UNITS)
+          if (dir_prev && k % kDirUnit == 0) put_edge(sp);   // plane k+1, staged in the step before
         if (k + LEAD <= kmax) store_k(k + LEAD);
         // PRO: coarse plane (k + 4) / 2 with fine plane k + 2 (k even), fetched
         // in the step before
