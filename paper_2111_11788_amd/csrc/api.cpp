@@ -70,12 +70,10 @@ int mlmc_create(const mlmc_config* cfg, mlmc_ctx** out) {
   std::vector<int> xperm(cfg->n_modes), xoff(ctx->K1 + 1, 0);
   for (int m = 0; m < cfg->n_modes; ++m) xoff[ctx->modes.triples[3 * m] + 1] += 1;
   for (int a = 0; a < ctx->K1; ++a) xoff[a + 1] += xoff[a];
-  // and within a group by their y-factor, so the modes of an (x, y) factor pair are consecutive
-  for (int m = 0; m < cfg->n_modes; ++m) xperm[m] = m;
-  const auto& tri = ctx->modes.triples;
-  std::stable_sort(xperm.begin(), xperm.end(), [&](int p, int q) {
-    return tri[3 * p] != tri[3 * q] ? tri[3 * p] < tri[3 * q] : tri[3 * p + 1] < tri[3 * q + 1];
-  });
+  {
+    std::vector<int> fill(xoff.begin(), xoff.end() - 1);
+    for (int m = 0; m < cfg->n_modes; ++m) xperm[fill[ctx->modes.triples[3 * m]]++] = m;
+  }
   if (e == hipSuccess)
     e = hipMemcpyAsync(ctx->d_xperm, xperm.data(), xperm.size() * sizeof(int), hipMemcpyHostToDevice, ctx->st);
   if (e == hipSuccess)

@@ -290,7 +290,7 @@ struct mlmc_ctx {
   int K1 = 0;
   double* d_sqrtlam = nullptr;
   int* d_triples = nullptr;
-  int* d_xperm = nullptr;         // the modes ordered by their x-factor, then their y-factor (stable)
+  int* d_xperm = nullptr;         // the modes ordered by their x-factor (stable)
   int* d_xoff = nullptr;          // [K1 + 1]: modes of x-factor a at d_xperm[xoff[a] .. xoff[a + 1])
   int field_kernel = 0;           // mlmc_tuning.field
   std::map<int, double*> d_tab;

@@ -16,7 +16,8 @@
 // row r to batch slot rowmap[r] (xi read from and kappa written to that slot).
 // The default evaluation for 64^3 to 256^3 meshes factorises the same sum
 // over the three axes and keeps only the final per-plane contraction, a
-// [n x K1] . [K1 x n] product, on the same instruction (k_field_plane_mfma).
+// [n x K1] . [K1 x n] product, on the same instruction (k_field_plane_mfma);
+// below 64^3 both sums of the row-wise form run on it (k_field_rows).
 #include <algorithm>
 
 #include "common.hpp"
@@ -408,124 +409,137 @@ void launch_field_plane_mfma(int n, int M, int K1, int64_t count, const double* 
                                                             tab, kappa, kappa32, rowmap);
 }
 
-// ------------------------------ the same factorised form on meshes below 64^3
-// A plane of these meshes is too small for a workgroup of its own, so a
-// workgroup takes UW consecutive planes ("units": a quarter of a 32^3 sample,
-// one 16^3 sample, four samples of 8^3 or 4^3) and forms A and B of SU units
-// at a time.  The element contraction is the plane kernel's, with rows of
-// fewer than 16 elements packed PACK = 16 / n to a tile row: a tile row's A
-// operand is the PACK rows of B one after another and the Phi_x operand is
-// block diagonal (zero where a column belongs to another row), so a tile
-// holds 256 consecutive elements on every mesh and no lane of the exponential
-// is idle.  LDS limits the workgroups per CU; SU = 4 (n >= 16) keeps it below
-// 40 KB at K1 = 16.
+// ------------------------------ the separable form on meshes below 64^3, on MFMA
+// The sums of k_field_sep, each in its order, on v_mfma_f64_16x16x4f64, which
+// adds its four products one after another as fused multiply-adds (so padding
+// with zeros changes nothing): the field has the bits of k_field_sep.  That
+// matters: a change in the last bit of kappa shows in Y = Q_l - Q_{l-1} of a
+// mixed-precision pair by up to 1e-8 of a nearly cancelling one.
+// A workgroup takes 16 samples and 16 element rows (fixed y, z).
+//   H[s][row][a] = sum over the modes m of x-factor a of xi[s][m] w[m][row]: a
+//     16 x 16 product of the samples' xi (staged in LDS) and the rows' factors
+//     w = sqrt(lambda_m) (phi_b(y) phi_c(z)), which each lane forms as it needs
+//     them; a wave takes every fourth a.
+//   g[row][ex] = sum_a H[row][a] phi_a(x_ex), SP samples at a time through LDS
+//     (over the xi).  Rows of fewer than 16 elements are packed PACK = 16 / n to
+//     a tile row: its operand is the PACK rows of H one after another, and the
+//     Phi_x operand is block diagonal (zero where a column belongs to another
+//     row), so a tile holds 256 elements on every mesh.
 // Bound: the 12 bytes written per element and the fp64 exponential (25 million
-// elements, 32^3 x 777, M = 256: 660 us with k_field_sep, whose element sums
-// read both operands from LDS, against 98 us a call here; the writes take 50 us).
+// elements, 32^3 x 777, M = 256: 102 us a call, 3.0 TB/s, against 731 us with
+// k_field_sep, whose sums read both operands from LDS; 13001 samples of 8^3, M =
+// 128: 207 -> 45 us; one of 16^3: 48 -> 7.5 us).  Chunks of 256 modes: 40 KB of LDS,
+// four workgroups per CU; 128 modes measured 113 us on the first of these.
+// modes of a chunk, samples of a pass, and the doubles that xi and H share
+constexpr int kRowsChunk = 256;
+__host__ __device__ constexpr int field_rows_chunk(int M) { return M < kRowsChunk ? M : kRowsChunk; }
+__host__ __device__ constexpr int field_rows_sp(int KS) { return KS == 2 ? 16 : 8; }
+__host__ __device__ constexpr int field_rows_shared(int KS, int pack, int M) {
+  const int x = 16 * (field_rows_chunk(M) | 1), h = field_rows_sp(KS) * 16 / pack * (4 * KS * pack + 1);
+  return x > h ? x : h;
+}
 template <int KS, int PACK, int CT>
-__global__ void __launch_bounds__(256) k_field_units(int n, int M, int K1, int UW, int SU, int64_t count,
-                                                     const double* __restrict__ xi,
-                                                     const double* __restrict__ sqrtlam,
-                                                     const int* __restrict__ triples,
-                                                     const int* __restrict__ xperm, const double* __restrict__ tab,
-                                                     double* __restrict__ kappa, float* __restrict__ kappa32,
-                                                     const int* __restrict__ rowmap) {
-  constexpr int KP = 4 * KS, KT = KP * PACK, PITCH = KT + 1;
+__global__ void __launch_bounds__(256) k_field_rows(int n, int M, int K1, int64_t count,
+                                                    const double* __restrict__ xi,
+                                                    const double* __restrict__ sqrtlam,
+                                                    const int* __restrict__ triples,
+                                                    const int* __restrict__ xperm, const int* __restrict__ xoff,
+                                                    const double* __restrict__ tab, double* __restrict__ kappa,
+                                                    float* __restrict__ kappa32, const int* __restrict__ rowmap) {
+  constexpr int KP = 4 * KS, KT = KP * PACK, PITCH = KT + 1, SP = field_rows_sp(KS);
   extern __shared__ double fsm[];
-  const int lg = 31 - __clz(n);
-  const int NS = UW > n ? UW >> lg : 1;               // samples of the workgroup
-  const int rows = SU << lg;                          // element rows of a pass
-  const int K2 = K1 * K1;
-  double* wv = fsm;                                   // [NS][M] sqrt(lambda) xi, (x, y)-grouped order
-  double* tz = wv + NS * M;                           // [n][K1] the table
-  double* A = tz + n * K1;                            // [SU][K1][K1]
-  double* Bm = A + SU * K2;                           // [rows / PACK][PITCH]
-  int* abo = reinterpret_cast<int*>(Bm + (rows / PACK) * PITCH);   // [K1^2 + 1] first mode of each (a, b)
-  int* cz = abo + K2 + 1;                             // [M] z-factor of each mode
-  const int tid = (int)threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int64_t unit0 = (int64_t)blockIdx.x * UW;     // units are numbered sample * n + plane
-  const int64_t s0 = unit0 >> lg;
-  for (int q = tid; q <= K2; q += 256) abo[q] = M;
-  for (int q = tid; q < NS * M; q += 256) {
-    const int s = q / M, p = q - (q / M) * M;
-    double v = 0.0;
-    if (s0 + s < count) {
-      const int m = xperm[p];
-      const int64_t r = rowmap ? rowmap[s0 + s] : s0 + s;
-      v = sqrtlam[m] * xi[r * M + m];
-    }
-    wv[q] = v;
-  }
+  const int lg = 31 - __clz(n), CH = field_rows_chunk(M), XP = CH | 1, lgp = CH > 1 ? 32 - __clz(CH - 1) : 0;
+  double* tz = fsm;                                   // [n][K1] the table
+  double* sl = tz + n * K1;                           // [CH] sqrt(lambda) of the chunk's modes
+  double* X = sl + CH;                                // [16][XP] xi of the chunk's modes; then
+  double* Hb = X;                                     // [SP * 16 / PACK][PITCH] H
+  int* bc = reinterpret_cast<int*>(X + field_rows_shared(KS, PACK, M));   // [CH] their y- and z-factors
+  const int tid = (int)threadIdx.x, lane = tid & 63, wave = tid >> 6, lc = lane & 15, lk = lane >> 4;
+  const int rows = n * n / 16;                        // row tiles of a sample
+  const int64_t s0 = (int64_t)(blockIdx.x / rows) * 16;
+  const int row0 = (int)(blockIdx.x % rows) * 16;
   for (int q = tid; q < n * K1; q += 256) tz[q] = tab[q];
-  __syncthreads();
-  // the first mode of every (a, b) at or after each pair: a mode that opens a
-  // new pair fills the entries since the pair before it
-  for (int p = tid; p < M; p += 256) {
-    const int m = xperm[p];
-    const int ab = triples[3 * m] * K1 + triples[3 * m + 1];
-    cz[p] = triples[3 * m + 2];
-    int prev = -1;
-    if (p > 0) {
-      const int mp = xperm[p - 1];
-      prev = triples[3 * mp] * K1 + triples[3 * mp + 1];
-    }
-    for (int q = prev + 1; q <= ab; ++q) abo[q] = p;
-  }
   // block-diagonal Phi_x: lane l supplies row k = 4 ks + l / 16 of column l % 16
   double ph[CT][KS * PACK];
 #pragma unroll
   for (int t = 0; t < CT; ++t)
 #pragma unroll
     for (int ks = 0; ks < KS * PACK; ++ks) {
-      const int k = 4 * ks + (lane >> 4), col = 16 * t + (lane & 15);
+      const int k = 4 * ks + lk, col = 16 * t + lc;
       const int pr = k / KP, a = k - pr * KP;          // packed row and x-factor of this k
       ph[t][ks] = (PACK == 1 || (col >> lg) == pr) && a < K1 ? tab[(col & (n - 1)) * K1 + a] : 0.0;
     }
-  const int64_t ne = (int64_t)1 << (3 * lg);
-  for (int u0 = 0; u0 < UW; u0 += SU) {
-    __syncthreads();   // the modes are staged; the previous pass's B is no longer read
-    for (int q = tid; q < SU * K2; q += 256) {
-      const int u = q / K2, ab = q - u * K2;
-      const int64_t w = unit0 + u0 + u;
-      const int z = (int)(w & (n - 1));
-      const double* x = wv + (int)((w >> lg) - s0) * M;
-      const double* tr = tz + z * K1;
-      double acc = 0.0;
-      for (int p = abo[ab]; p < abo[ab + 1]; ++p) acc = fma(x[p], tr[cz[p]], acc);
-      A[q] = acc;
-    }
-    __syncthreads();
-    for (int q = tid; q < rows * KP; q += 256) {
-      const int yr = q / KP, a = q - yr * KP;
-      double acc = 0.0;
-      if (a < K1) {
-        const double* ty = tz + (yr & (n - 1)) * K1;
-        const double* Aa = A + (yr >> lg) * K2 + a * K1;
-        for (int b = 0; b < K1; ++b) acc = fma(Aa[b], ty[b], acc);
+  d4 h[KS];   // H of the x-factors wave, wave + 4, ..: samples lk + 4 q, row lc
+#pragma unroll
+  for (int i = 0; i < KS; ++i) h[i] = d4{0.0, 0.0, 0.0, 0.0};
+  for (int c0 = 0; c0 < M; c0 += CH) {   // a chunk of modes, in x-grouped order
+    if (c0) __syncthreads();             // the chunk before is no longer read
+    const int p = tid & ((1 << lgp) - 1);   // the threads stage 2^lgp modes of 256 >> lgp samples at a time
+    if (p < CH && c0 + p < M) {
+      const int m = xperm[c0 + p];
+      if (tid >> lgp == 0) {
+        sl[p] = sqrtlam[m];
+        bc[p] = triples[3 * m + 1] | (triples[3 * m + 2] << 16);
       }
-      Bm[(yr / PACK) * PITCH + (yr % PACK) * KP + a] = acc;
+      for (int s = tid >> lgp; s < 16; s += 256 >> lgp) {
+        double v = 0.0;
+        if (s0 + s < count) {
+          const int64_t r = rowmap ? rowmap[s0 + s] : s0 + s;
+          v = xi[r * M + m];
+        }
+        X[s * XP + p] = v;
+      }
     }
     __syncthreads();
-    for (int rt = wave; rt < rows / (16 * PACK); rt += 4) {
+    const double* ty = tz + ((row0 + lc) & (n - 1)) * K1;
+    const double* tt = tz + ((row0 + lc) >> lg) * K1;
+    const double* x = X + lc * XP;
+#pragma unroll
+    for (int i = 0; i < KS; ++i) {
+      const int a = wave + 4 * i;
+      if (a < K1) {
+        const int from = xoff[a] - c0, to = xoff[a + 1] - c0;
+        const int p1 = to < CH ? to : CH;
+        for (int p0 = from > 0 ? from : 0; p0 < p1; p0 += 4) {
+          const bool in = p0 + lk < p1;
+          const int p = in ? p0 + lk : p0;
+          const double xv = x[p], w = sl[p] * (ty[bc[p] & 0xffff] * tt[bc[p] >> 16]);
+          h[i] = __builtin_amdgcn_mfma_f64_16x16x4f64(in ? xv : 0.0, in ? w : 0.0, h[i], 0, 0, 0);
+        }
+      }
+    }
+  }
+  const int64_t ne = (int64_t)1 << (3 * lg);
+#pragma unroll
+  for (int f = 0; f < 16 / SP; ++f) {   // samples f SP ..
+    if (s0 + f * SP >= count) break;    // uniform over the workgroup
+    __syncthreads();                    // the xi or the H before are no longer read
+#pragma unroll
+    for (int i = 0; i < KS; ++i)
+#pragma unroll
+      for (int q = 0; q < SP / 4; ++q) {
+        const int rho = (lk + 4 * q) * 16 + lc;
+        Hb[(rho / PACK) * PITCH + (rho % PACK) * KP + wave + 4 * i] = h[i][f * (SP / 4) + q];
+      }
+    __syncthreads();
+    for (int t = wave; t < SP / PACK && s0 + f * SP + t * PACK < count; t += 4) {   // a tile: PACK samples
       double av[KS * PACK];
 #pragma unroll
-      for (int ks = 0; ks < KS * PACK; ++ks) av[ks] = Bm[(16 * rt + (lane & 15)) * PITCH + 4 * ks + (lane >> 4)];
+      for (int ks = 0; ks < KS * PACK; ++ks) av[ks] = Hb[(16 * t + lc) * PITCH + 4 * ks + lk];
 #pragma unroll
-      for (int t = 0; t < CT; ++t) {
+      for (int c = 0; c < CT; ++c) {
         d4 acc = d4{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
         for (int ks = 0; ks < KS * PACK; ++ks)
-          acc = __builtin_amdgcn_mfma_f64_16x16x4f64(av[ks], ph[t][ks], acc, 0, 0, 0);
+          acc = __builtin_amdgcn_mfma_f64_16x16x4f64(av[ks], ph[c][ks], acc, 0, 0, 0);
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-          // element of the workgroup's units, counted from unit0 + u0
-          const int e = ((16 * rt + (lane >> 4) + 4 * q) * CT + t) * 16 + (lane & 15);
-          const int64_t ge = ((unit0 + u0) << (2 * lg)) + e;
-          const int64_t s = ge >> (3 * lg);
+          const int rho = (16 * t + lk + 4 * q) * PACK + (PACK > 1 ? lc >> lg : 0);
+          const int64_t s = s0 + f * SP + (rho >> 4);
           if (s < count) {
             const int64_t r = rowmap ? rowmap[s] : s;
             const double k = exp(acc[q]);
-            const int64_t at = r * ne + (ge & (ne - 1));
+            const int64_t at = r * ne + (row0 + (rho & 15)) * n + ((16 * c + lc) & (n - 1));
             kappa[at] = k;
             if (kappa32) kappa32[at] = (float)k;
           }
@@ -535,42 +549,29 @@ __global__ void __launch_bounds__(256) k_field_units(int n, int M, int K1, int U
   }
 }
 
-// Units per workgroup and per pass of k_field_units, and its LDS; false where
-// the mesh has another form or the pass does not fit 64 KiB
-struct UnitGeom {
-  int UW = 0, SU = 0;
-  size_t lds = 0;
-};
-bool field_units_geom(int n, int M, int K1, UnitGeom* g) {
-  if (K1 > 32) return false;
-  const int KP = K1 <= 8 ? 8 : (K1 <= 16 ? 16 : 32);
-  switch (n) {
-    case 4: g->UW = 16; g->SU = 16; break;   // one tile
-    case 8: g->UW = 32; g->SU = 16; break;   // four tiles, one per wave
-    case 16: g->UW = 16; g->SU = 4; break;   // likewise
-    case 32: g->UW = 8; g->SU = 4; break;
-    default: return false;
-  }
-  const int pack = n < 16 ? 16 / n : 1, NS = g->UW > n ? g->UW / n : 1, rows = g->SU * n;
-  g->lds = ((size_t)NS * M + (size_t)n * K1 + (size_t)g->SU * K1 * K1 + (size_t)(rows / pack) * (KP * pack + 1)) *
-               sizeof(double) +
-           ((size_t)K1 * K1 + 1 + M) * sizeof(int);
-  return g->lds <= 65536;
+// LDS of k_field_rows (at most 49 KiB); 0 where the mesh has another form or
+// k_field_sep, whose sums these are, would not run
+size_t field_rows_lds(int n, int M, int K1) {
+  if (n < 4 || n > 32 || K1 > 32 || 2 * (int64_t)M + (int64_t)K1 * (n + 1) > 65536 / (int64_t)sizeof(double)) return 0;
+  const int KS = K1 <= 8 ? 2 : (K1 <= 16 ? 4 : 8), pack = n < 16 ? 16 / n : 1;
+  const int ch = field_rows_chunk(M);
+  return ((size_t)n * K1 + (size_t)ch + (size_t)field_rows_shared(KS, pack, M)) * sizeof(double) +
+         (size_t)ch * sizeof(int);
 }
 
 template <int KS>
-void launch_field_units_n(int n, int M, int K1, const UnitGeom& g, int64_t count, const double* xi,
-                          const double* sqrtlam, const int* triples, const int* xperm, const double* tab,
-                          double* kappa, float* kappa32, const int* rowmap, hipStream_t st) {
-  const dim3 grid((unsigned)((count * n + g.UW - 1) / g.UW));
-#define MLMC_UNITS(PACK, CT)                                                                                      \
-  k_field_units<KS, PACK, CT><<<grid, dim3(256), g.lds, st>>>(n, M, K1, g.UW, g.SU, count, xi, sqrtlam, triples, \
-                                                              xperm, tab, kappa, kappa32, rowmap)
-  if (n == 4) MLMC_UNITS(4, 1);
-  else if (n == 8) MLMC_UNITS(2, 1);
-  else if (n == 16) MLMC_UNITS(1, 1);
-  else MLMC_UNITS(1, 2);
-#undef MLMC_UNITS
+void launch_field_rows_n(int n, int M, int K1, size_t lds, int64_t count, const double* xi, const double* sqrtlam,
+                         const int* triples, const int* xperm, const int* xoff, const double* tab, double* kappa,
+                         float* kappa32, const int* rowmap, hipStream_t st) {
+  const dim3 grid((unsigned)((count + 15) / 16 * (n * n / 16)));
+#define MLMC_ROWS(PACK, CT)                                                                                        \
+  k_field_rows<KS, PACK, CT><<<grid, dim3(256), lds, st>>>(n, M, K1, count, xi, sqrtlam, triples, xperm, xoff, tab, \
+                                                           kappa, kappa32, rowmap)
+  if (n == 4) MLMC_ROWS(4, 1);
+  else if (n == 8) MLMC_ROWS(2, 1);
+  else if (n == 16) MLMC_ROWS(1, 1);
+  else MLMC_ROWS(1, 2);
+#undef MLMC_ROWS
 }
 
 template <int KS>
@@ -597,13 +598,12 @@ hipError_t launch_field(int n, int M, int64_t count, const double* xi, const dou
     else launch_field_plane_mfma_n<8>(n, M, K1, count, xi, sqrtlam, triples, xperm, xoff, tab, kappa, kappa32, rowmap, st);
     return hipGetLastError();
   }
-  // 4^3 to 32^3: several planes per workgroup (one block per UW planes: within
-  // the launch limit for any count whose kappa fits the card)
-  UnitGeom ug;
-  if (!bf16 && xperm && xoff && field_units_geom(n, M, K1, &ug) && (count * n + ug.UW - 1) / ug.UW <= 0x7fffffff) {
-    if (K1 <= 8) launch_field_units_n<2>(n, M, K1, ug, count, xi, sqrtlam, triples, xperm, tab, kappa, kappa32, rowmap, st);
-    else if (K1 <= 16) launch_field_units_n<4>(n, M, K1, ug, count, xi, sqrtlam, triples, xperm, tab, kappa, kappa32, rowmap, st);
-    else launch_field_units_n<8>(n, M, K1, ug, count, xi, sqrtlam, triples, xperm, tab, kappa, kappa32, rowmap, st);
+  // 4^3 to 32^3: 16 samples and 16 element rows per workgroup
+  const size_t rlds = !bf16 && xperm && xoff ? field_rows_lds(n, M, K1) : 0;
+  if (rlds && (count + 15) / 16 * (n * n / 16) <= 0x7fffffff) {
+    if (K1 <= 8) launch_field_rows_n<2>(n, M, K1, rlds, count, xi, sqrtlam, triples, xperm, xoff, tab, kappa, kappa32, rowmap, st);
+    else if (K1 <= 16) launch_field_rows_n<4>(n, M, K1, rlds, count, xi, sqrtlam, triples, xperm, xoff, tab, kappa, kappa32, rowmap, st);
+    else launch_field_rows_n<8>(n, M, K1, rlds, count, xi, sqrtlam, triples, xperm, xoff, tab, kappa, kappa32, rowmap, st);
     return hipGetLastError();
   }
   if (!bf16 && xperm && xoff) {

@@ -8,6 +8,7 @@ pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
 
 import paper_2111_11788_amd as mm
+from oracle import field, rng
 from workloads import Workload
 
 
@@ -27,3 +28,41 @@ def test_y_of_fine_pairs_keeps_its_value(corr, M, first, want):
     ctx.close()
     want = np.array([float.fromhex(w) for w in want])
     assert np.linalg.norm(y - want) <= 1e-9 * np.linalg.norm(want)
+
+
+# the same for one 64^3 / 32^3 pair: the field of the 32^3 mesh in its last bit (its
+# sums in another order move these by 4e-9 to 3e-8)
+@pytest.mark.parametrize("corr,M,first,want", [(0.2, 8, 638, "0x1.b5d9b3d7e0000p-20"),
+                                               (0.1, 8, 654, "0x1.357f0f79f4000p-18"),
+                                               (0.5, 64, 679, "-0x1.13668a0d20000p-19")])
+def test_y_of_a_middle_pair_keeps_its_value(corr, M, first, want):
+    wl = Workload("pair", n0=32, levels=2, sigma2=1.0, corr_len=corr, n_modes=M, qoi=1, rtol=1e-8, max_iter=1000,
+                  solver=0, precision=1, batch=8)
+    ctx = mm.Context(wl, arena_bytes=1 << 30)
+    y = ctx.sample_level(1, first, 1)[0][0]
+    ctx.close()
+    want = float.fromhex(want)
+    assert abs(y - want) <= 1e-9 * abs(want)
+
+
+# the field below 64^3 on every shape of its kernel: more modes than a chunk holds
+# (and a group of one x-factor across two chunks), one to three x-factor blocks
+# a wave, samples on both sides of 16 and of a pass; against the oracle (the sums
+# differ in order only: exp turns an absolute error of a few 1e-15 times |g| <= ~10
+# into a relative one), and one sample alone, bit for bit
+@pytest.mark.parametrize("n,M,corr,count", [(4, 1, 0.5, 17), (4, 300, 0.1, 33), (8, 257, 0.2, 16), (8, 600, 0.05, 9),
+                                            (16, 256, 0.1, 25), (16, 1024, 0.05, 8), (32, 513, 0.1, 18),
+                                            (32, 2000, 0.1, 2)])
+def test_field_rows(n, M, corr, count):
+    wl = Workload("rows", n0=n, levels=1, sigma2=1.0, corr_len=corr, n_modes=M, qoi=0, rtol=1e-8, max_iter=10,
+                  solver=0, precision=1, batch=8)
+    ctx = mm.Context(wl, arena_bytes=64 << 20)
+    xi = ctx.draw_xi(0, 5, count)
+    k, k32 = ctx.field(n, xi, want32=True)
+    want = field.kappa(n, corr, 1.0, M, rng.draw_xi(wl.seed, 0, 5, count, M))
+    got = k.cpu().numpy()
+    assert np.max(np.abs(got - want) / want) < 1e-13
+    assert np.array_equal(k32.cpu().numpy(), got.astype(np.float32))
+    for s in (0, count // 2, count - 1):
+        assert torch.equal(ctx.field(n, xi[s:s + 1])[0], k[s])
+    ctx.close()
