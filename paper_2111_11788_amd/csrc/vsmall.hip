@@ -279,7 +279,7 @@ __device__ __forceinline__ void q1v_chain(const Own<n>& o, const T* u, const T* 
 }
 
 // The same one element row at a time: fewer values live (62 registers in fp64),
-// more row reads.  For fp64 operators beside a solve's fp32 state, and in
+// more row reads.  For the true residual of fp64 solves, and their operator in
 // workgroups of 16 waves.
 template <int n, class T>
 __device__ __forceinline__ void q1v_rows(const Own<n>& o, const T* u, const T* kap, T (&au)[4]) {
@@ -311,6 +311,108 @@ __device__ __forceinline__ void q1v_rows(const Own<n>& o, const T* u, const T* k
   const T h12 = T(1) / T(12 * n);
 #pragma unroll
   for (int v = 0; v < 4; ++v) au[v] = (v > 0 || o.gx != 0) ? h12 * fma(ks[v] * uc[v], T(4), -f[v]) : T(0);
+}
+
+// r <- r - A u at the thread's nodes in fp64, for the refinement of mixed-precision
+// solves, one row of u at a time (few values live beside the fp32 state).  The
+// operations, each rounding included, are those of the refinement these meshes
+// had before whole solves took its place (16^3: the LDS-tiled engine's, 8^3 and
+// 4^3: element by element): the first refinement's r is what is left of a
+// cancellation, and how it rounds shows in Y of a pair through the solve that
+// follows (one-sample 32^3 / 16^3 pairs: up to 1e-8 of a nearly cancelling Y).
+template <int n>
+__device__ __forceinline__ void residual4(const Own<n>& o, const double* u, const double* kap, double (&r)[4]) {
+  constexpr int n2 = n * n;
+  constexpr double h = 1.0 / n;
+  const double* up = u + o.pos;
+  const double* kp = kap + o.pos - n - n2;
+  double f[4], ks[4], K0[5], K1[5], q[6];
+  if constexpr (n == 16) {
+    {
+      double C[5];
+#pragma unroll
+      for (int dy = 0; dy < 2; ++dy) {
+        o.krow(kp + n * dy, K0);
+        o.krow(kp + n * dy + n2, K1);
+        o.urow(up + n * (2 * dy - 1), q);
+#pragma unroll
+        for (int c = 0; c < 5; ++c) {
+          K0[c] += K1[c];
+          C[c] = dy ? C[c] + K0[c] : K0[c];
+        }
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          // that engine's threads own two nodes: which of the first two products
+          // is the rounded one differs between them
+          if (dy == 0)
+            f[v] = v & 1 ? fma(K0[v], q[v], K0[v + 1] * q[v + 2]) : fma(K0[v + 1], q[v + 2], K0[v] * q[v]);
+          else
+            f[v] = fma(K0[v + 1], q[v + 2], fma(K0[v], q[v], f[v]));
+        }
+      }
+#pragma unroll
+      for (int v = 0; v < 4; ++v) ks[v] = C[v] + C[v + 1];
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int dz = 0; dz < 2; ++dz) {
+      const double* z = up + n2 * (2 * dz - 1);
+      o.krow(kp + n2 * dz, K0);
+      o.krow(kp + n2 * dz + n, K1);
+      o.urow(z - n, q);
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        f[v] = fma(K0[v] + K0[v + 1], q[v + 1], f[v]);
+        f[v] = fma(K0[v], q[v], f[v]);
+        f[v] = fma(K0[v + 1], q[v + 2], f[v]);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      o.urow(z, q);
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        f[v] = fma(K0[v] + K1[v], q[v], f[v]);
+        f[v] = fma(K0[v + 1] + K1[v + 1], q[v + 2], f[v]);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      o.urow(z + n, q);
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        f[v] = fma(K1[v] + K1[v + 1], q[v + 1], f[v]);
+        f[v] = fma(K1[v], q[v], f[v]);
+        f[v] = fma(K1[v + 1], q[v + 2], f[v]);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    ld4(up, q);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) r[v] = fma(-(h * (1.0 / 12.0)), fma(ks[v] * q[v], 4.0, -f[v]), r[v]);
+  } else {
+#pragma unroll
+    for (int v = 0; v < 4; ++v) f[v] = ks[v] = 0.0;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int sz = e >> 1, sy = e & 1, oz = n2 * (2 * sz - 1), oy = n * (2 * sy - 1);
+      double m[6], w[6];
+      o.krow(kp + n2 * sz + n * sy, K0);
+      o.urow(up + oy, m);
+      o.urow(up + oz, w);
+      o.urow(up + oy + oz, q);
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+#pragma unroll
+        for (int sx = 0; sx < 2; ++sx) {
+          const double kv = K0[v + sx];
+          const double g = (m[v + 2 * sx] + w[v + 2 * sx]) + (q[v + 1] + q[v + 2 * sx]);
+          ks[v] += kv;
+          f[v] = fma(kv, g, f[v]);
+        }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    ld4(up, q);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) r[v] = fma(-h, fma(ks[v] * q[v], 1.0 / 3.0, -(f[v] * (1.0 / 12.0))), r[v]);
+  }
+  if (o.gx == 0) r[0] = 0.0;
 }
 
 // D, the Jacobi diagonal, from the kappa sums
@@ -812,12 +914,7 @@ __global__ void __launch_bounds__(small_threads<NL>(), NL == 2 ? 1 : 4) k_solve_
     }
     __syncthreads();
     rhs(r64);
-    if (o.has) {
-      double au[4];
-      q1v_rows<n>(o, U, kg, au);
-#pragma unroll
-      for (int v = 0; v < 4; ++v) r64[v] -= au[v];
-    }
+    if (o.has) residual4<n>(o, U, kg, r64);
     rr_last = sum(dot4(r64, r64));
     done = rr_last <= a.rtol2 * bb || !isfinite(rr_last);
     zero(lv.X[0][0], lv.X[0][0] + 2 * S);   // (every thread is past the operator: the sum's barrier)

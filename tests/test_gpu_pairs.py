@@ -45,6 +45,21 @@ def test_y_of_a_middle_pair_keeps_its_value(corr, M, first, want):
     assert abs(y - want) <= 1e-9 * abs(want)
 
 
+# and for one 32^3 / 16^3 pair: the fp64 refinement of the 16^3 whole solve (another
+# order of its operations moves these by 5e-9 to 3e-8)
+@pytest.mark.parametrize("corr,M,first,want", [(0.5, 8, 582, "0x1.4f5fa37bc0000p-22"),
+                                               (0.5, 8, 386, "-0x1.0184e5f3d8000p-20"),
+                                               (0.5, 64, 792, "-0x1.6b9efbb2c0000p-21")])
+def test_y_of_a_small_pair_keeps_its_value(corr, M, first, want):
+    wl = Workload("pair", n0=16, levels=2, sigma2=1.0, corr_len=corr, n_modes=M, qoi=1, rtol=1e-8, max_iter=1000,
+                  solver=0, precision=1, batch=8)
+    ctx = mm.Context(wl, arena_bytes=1 << 30)
+    y = ctx.sample_level(1, first, 1)[0][0]
+    ctx.close()
+    want = float.fromhex(want)
+    assert abs(y - want) <= 1e-9 * abs(want)
+
+
 # the field below 64^3 on every shape of its kernel: more modes than a chunk holds
 # (and a group of one x-factor across two chunks), one to three x-factor blocks
 # a wave, samples on both sides of 16 and of a pass; against the oracle (the sums
