@@ -1111,6 +1111,12 @@ int run_round(mlmc_ctx* ctx, std::vector<LevelReq>& reqs, bool record) {
     ln.tasks.clear();
     off += lane_bytes[i];
   }
+  // lanes that sit this round out: it writes over their ranges, so they are
+  // carved and cleared again when next used
+  for (size_t i = (size_t)K; i < ctx->lanes.size(); ++i) {
+    ctx->lanes[i]->w.sw.release_graphs();
+    ctx->lanes[i]->key = std::make_tuple(-1, -1, -1);
+  }
   for (size_t i = 0; i < ts.size(); ++i) ctx->lanes[ts[i].lane]->tasks.push_back((int)i);
   double* dqf = reinterpret_cast<double*>((char*)c.arena + (c.arena_bytes - qbytes) / 256 * 256);
   double* dqc = dqf + align256(total * sizeof(double)) / sizeof(double);

@@ -165,3 +165,27 @@ def test_nonfinite_coefficient_stops_the_solve(dev, n, precision):
     assert it[1] < 100
     uc = u.cpu().numpy()
     assert np.all(np.isfinite(uc[0])) and np.all(np.isfinite(uc[2]))
+
+
+# a round that the arena holds on two lanes only, between two rounds on four: it
+# writes over the ranges of the lanes it leaves out, whose work spaces hold zero
+# boundaries and counters for the next round
+def test_a_round_on_fewer_lanes_leaves_no_stale_work_space():
+    wl = _wl(n0=8, levels=3, rtol=1e-9, batch=16)
+    cfg = mm.make_config(wl)
+    small = mm.workspace_bytes(cfg, 2, 16)       # 7 batches of 16: four lanes, the last with the coarse solves
+    cap = int(16 * (31 ** 3 + 15 ** 3) / 7 ** 3)
+    large = mm.workspace_bytes(cfg, 0, cap)      # four batches of a coarse level's capacity
+    arena = max(4 * small, 2 * large) + (1 << 20)
+    assert 3 * large > arena + (2 << 20)
+    ctx = mm.Context(wl, arena_bytes=arena)
+    first = ctx.sample_level(2, 0, 112)
+    lanes = [p["lane"] for p in ctx.last_plan()]
+    assert max(lanes) == 3 and [p["n"] for p in ctx.last_plan() if p["lane"] == 2] == [32, 32]
+    ctx.sample_level(0, 0, 4 * cap)
+    assert max(p["lane"] for p in ctx.last_plan()) == 1
+    again = ctx.sample_level(2, 0, 112)
+    assert [p["lane"] for p in ctx.last_plan()] == lanes
+    ctx.close()
+    for a, b in zip(first, again):
+        assert np.array_equal(a, b)
