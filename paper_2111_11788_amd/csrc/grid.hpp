@@ -17,8 +17,12 @@ struct ZV { static constexpr int V = 16 / (int)sizeof(T); };
 // chunk of planes; a workgroup holds `rows` rows of one sample and one plane
 // chunk.  Workgroups of a sample are numbered rb + row_blocks * zb.  Partial
 // sums are taken per row block and unit of `zu` planes (planes 1 + u zu ..
-// (u + 1) zu; a chunk is a whole number of units), numbered rb + row_blocks *
-// u, so up to 64^3 they do not depend on how the planes are split.
+// (u + 1) zu; a chunk is a whole number of units) and added up in an order that
+// does not depend on how the planes are split, and so not on the batch: up to
+// 64^3 a workgroup stores every unit's sum, numbered rb + row_blocks * u; above
+// (fold) a chunk is 2^k units, aligned, and its workgroup adds them by pairs, the
+// pairs by pairs and so on, stores one sum, numbered as the workgroup, and the
+// reduction goes on in the same tree over the chunks.
 struct ZGeom {
   int n = 0;
   int G = 0;            // vector groups per row (n / V)
@@ -26,10 +30,17 @@ struct ZGeom {
   int row_blocks = 0;   // workgroups per plane chunk
   int zc = 1;           // plane chunks
   int zlen = 0;         // planes per chunk
-  int zu = 1;           // planes per partial sum
+  int zu = 1;           // planes per unit
+  bool fold = false;    // one partial sum per chunk
   int threads = 256;    // threads per workgroup
   __host__ __device__ uint32_t blocks() const { return (uint32_t)row_blocks * zc; }
-  __host__ __device__ uint32_t parts() const { return (uint32_t)row_blocks * ((n - 1 + zu - 1) / zu); }
+  __host__ __device__ uint32_t parts() const { return fold ? blocks() : (uint32_t)row_blocks * ((n - 1 + zu - 1) / zu); }
+  // what a reduction is given: the partial sums, and with fold log2 of the chunks in bits 24..
+  uint32_t parts_code() const {
+    uint32_t lz = 0;
+    while (fold && (1 << lz) < zc) ++lz;
+    return parts() | lz << 24;
+  }
 };
 
 // waves of a launch from which the samples' planes are no longer split
@@ -61,12 +72,14 @@ inline void zsplit(ZGeom& g, long waves) {
     }
     return;
   }
-  // larger meshes: one partial sum per chunk, chunks of at least 8 planes
+  // larger meshes: one partial sum per chunk, chunks of at least 8 planes (n / zc,
+  // a power of two: n and zc are)
   int zc = 1;
   while (waves * zc < kFillWaves && (n - 1) / (zc * 2) >= 8) zc *= 2;
   g.zc = zc;
   g.zlen = (n - 1 + zc - 1) / zc;
-  g.zu = g.zlen;
+  g.zu = 8;
+  g.fold = true;
 }
 
 template <class T>
@@ -134,10 +147,10 @@ inline ZGeom zgeom_tall(int n, int B) {
 
 // The planes of an LDS-engine launch of B samples split further while it is
 // below kSplitWaves.  zsplit stops at chunks that keep a sample's partial sums
-// few (8 planes at 64^3, 4 below, 16 at 128^3); a launch without sums, and above 64^3 one whose sums fit
-// `cap` per sample (~0: no sums), goes down to 8 planes above 64^3, 4 at 64^3
-// and 2 below: what a chunk stages beyond its own planes is cheap while the
-// chip is not full.  A solve of three 128^3 samples: 2.70 -> 2.36 ms with the
+// few (8 planes at 64^3, 4 below, 16 at 128^3); a launch without sums, and above 64^3
+// one whose sums fit `cap` per sample (~0: no sums), goes down to 8 planes above
+// 64^3, 4 at 64^3 and 2 below: what a chunk stages beyond its own planes is cheap
+// while the chip is not full.  A solve of three 128^3 samples: 2.70 -> 2.36 ms with the
 // split above 64^3 (4 planes in place of 8: 2.42), 2.15 ms with the levels below as
 // well; 32 pairs of 32^3 / 16^3, mixed: 1.05 -> 1.00 ms.
 inline ZGeom zfine(ZGeom g, int B, uint32_t cap = ~0u) {
@@ -147,7 +160,6 @@ inline ZGeom zfine(ZGeom g, int B, uint32_t cap = ~0u) {
   while (waves * g.zc < kSplitWaves && g.zlen % (2 * least) == 0 && (cap == ~0u || 2 * g.parts() <= cap)) {
     g.zlen /= 2;
     g.zc = (g.n - 1 + g.zlen - 1) / g.zlen;
-    if (g.n > 64) g.zu = g.zlen;
   }
   return g;
 }

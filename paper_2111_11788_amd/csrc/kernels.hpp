@@ -255,6 +255,8 @@ enum ReduceOp : int {
 // The RR ops treat a NaN or Inf sum as the end of the sample's solve (active
 // 0, or the DONE / TRANSITION phase), keeping the value in rr so the caller can
 // tell it from convergence.
+// nparts: as the launch that wrote the partial sums returned it (the z-march
+// kernels: ZGeom::parts_code).
 // h_count (may be null; pinned host memory): receives the number of samples
 // active after the op, for B <= kCountInReduce samples.
 hipError_t launch_reduce(int B, int op, double tol2, uint32_t nparts, SolveState s, double* out,

@@ -380,15 +380,42 @@ __device__ __forceinline__ void count_on_host(unsigned long long* ticket, int* h
   }
 }
 
-// one workgroup per sample: fixed-order sum of its partials, then the scalar op
-__global__ void __launch_bounds__(kBlock) k_reduce(int op, double tol2, uint32_t nparts, SolveState st, double* out,
-                                                   int* h_count) {
+// The sum of 16 values by pairs, the pairs by pairs and so on
+__device__ __forceinline__ double pair_sum16(double (&v)[16]) {
+#pragma unroll
+  for (int d = 1; d < 16; d *= 2)
+#pragma unroll
+    for (int k = 0; k < 16; k += 2 * d) v[k] += v[k + d];
+  return v[0];
+}
+// The same of 2^lz values `stride` apart (lz <= 7; the missing ones of a shorter tree are zeros)
+__device__ __forceinline__ double pair_sum(const double* p, size_t stride, uint32_t lz) {
+  const uint32_t count = 1u << lz;
+  double r[16];
+#pragma unroll
+  for (uint32_t q = 0; q < 16; ++q) {
+    r[q] = 0.0;
+    if (16 * q < count && q < 8) {   // uniform
+      double v[16];
+#pragma unroll
+      for (uint32_t k = 0; k < 16; ++k) v[k] = 16 * q + k < count ? p[(16 * q + k) * stride] : 0.0;
+      r[q] = pair_sum16(v);
+    }
+  }
+  return pair_sum16(r);
+}
+
+// one workgroup per sample: fixed-order sum of its partials, over the chunks of
+// planes first (lz: see ZGeom), then the scalar op
+__global__ void __launch_bounds__(kBlock) k_reduce(int op, double tol2, uint32_t nparts, uint32_t lz, SolveState st,
+                                                   double* out, int* h_count) {
   const int b = blockIdx.x;
   const bool on = op == RED_STORE || !st.active || st.active[b];
   if (on) {   // uniform over the workgroup
     const double* p = st.partial + (size_t)b * st.pstride;
     double v = 0.0;
-    for (uint32_t c = threadIdx.x; c < nparts; c += kBlock) v += p[c];
+    const uint32_t rows = nparts >> lz;
+    for (uint32_t c = threadIdx.x; c < rows; c += kBlock) v += lz ? pair_sum(p + c, rows, lz) : p[c];
     v = block_sum(v);
     if (threadIdx.x == 0) reduce_op(op, tol2, st, out, b, v);
   }
@@ -726,10 +753,11 @@ hipError_t launch_level_stats(int njobs, const StatsJobs& jobs, hipStream_t st) 
 
 hipError_t launch_reduce(int B, int op, double tol2, uint32_t nparts, SolveState s, double* out, hipStream_t st,
                          int* h_count) {
-  if (nparts <= 64)
-    k_reduce_wave<<<dim3((B + kBlock / 64 - 1) / (kBlock / 64)), kBlock, 0, st>>>(B, op, tol2, nparts, s, out, h_count);
+  const uint32_t np = nparts & 0xffffff, lz = nparts >> 24;
+  if (np <= 64 && !lz)
+    k_reduce_wave<<<dim3((B + kBlock / 64 - 1) / (kBlock / 64)), kBlock, 0, st>>>(B, op, tol2, np, s, out, h_count);
   else
-    k_reduce<<<dim3(B), kBlock, 0, st>>>(op, tol2, nparts, s, out, h_count);
+    k_reduce<<<dim3(B), kBlock, 0, st>>>(op, tol2, np, lz, s, out, h_count);
   return hipGetLastError();
 }
 

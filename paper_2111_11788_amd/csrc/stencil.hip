@@ -57,19 +57,31 @@ __device__ __forceinline__ double wave_sum63(double v) {
   return v;
 }
 
-// out = the workgroup's sum of v, taken by every thread of it (waves in
-// order).  Two calls need a barrier between them beyond the one in here.
-__device__ __forceinline__ void unit_sum(double v, double* out) {
-  __shared__ double wsum[8];   // at most 512 threads
-  v = wave_sum63(v);
+// After plane k of the chunk k0 .. k1 - 1: at the end of a unit of planes (see
+// ZGeom), the workgroup's sum of acc (waves in order) to the sample's partial
+// sums.  Called by every thread; two sums need a barrier between them beyond the
+// one in here.
+__device__ __forceinline__ void unit_end(const ZGeom& g, double& acc, int k, int k0, int k1, double* part, int rb,
+                                         int zb) {
+  if (k % g.zu != 0 && k != k1 - 1) return;
+  __shared__ double wsum[8];    // at most 512 threads
+  __shared__ double pairs[8];   // fold: sums of 2^l units that wait for the 2^l after them (n <= 1024: 128 units)
+  const double v = wave_sum63(acc);
+  acc = 0.0;
   if ((threadIdx.x & 63) == 63) wsum[threadIdx.x >> 6] = v;
   __syncthreads();
-  if (threadIdx.x == 0) {
-    double t = 0.0;
-    const int nw = blockDim.x >> 6;
-    for (int w = 0; w < nw; ++w) t += wsum[w];
-    *out = t;
+  if (threadIdx.x != 0) return;
+  double t = 0.0;
+  const int nw = blockDim.x >> 6;
+  for (int w = 0; w < nw; ++w) t += wsum[w];
+  if (!g.fold) {
+    part[(size_t)((k - 1) / g.zu) * g.row_blocks + rb] = t;
+    return;
   }
+  int l = 0;
+  for (int u = (k - k0) / g.zu; u & 1; u >>= 1) t = pairs[l++] + t;
+  if (k == k1 - 1) part[(size_t)zb * g.row_blocks + rb] = t;
+  else pairs[l] = t;
 }
 
 __device__ __forceinline__ double block_sum(double v) {
@@ -847,10 +859,9 @@ __global__ void __launch_bounds__(256) k_zmarch(ZGeom g, size_t stride, T h, con
         dg[v] = h * ks * third;
       }
       if (valid) epi((size_t)b * stride + i0 + (size_t)n * j + (size_t)n2 * k, au, dg, uc, ok, acc);
-      if (Epi::kReduce && (k % g.zu == 0 || k == k1 - 1)) {   // the last plane of a unit
-        unit_sum(acc, partial + (size_t)b * pstride + (size_t)((k - 1) / g.zu) * g.row_blocks + rb);
-        acc = 0.0;
-        __syncthreads();
+      if (Epi::kReduce) {
+        unit_end(g, acc, k, k0, k1, partial + (size_t)b * pstride, rb, zb);
+        if (k % g.zu == 0) __syncthreads();   // uniform; before the next sum
       }
       if (NEED_U) {
 #pragma unroll
@@ -1346,11 +1357,8 @@ __global__ void __launch_bounds__(HALO == HALO_LDS ? 512 : 256) k_zlds(ZGeom g, 
         }
         epi(pos0 + (size_t)n2 * (k - k0), au, dg, uc, ok, acc);
       }
-      // the last plane of a unit (the next sum is a plane's barriers away)
-      if (Epi::kReduce && (k % g.zu == 0 || k == k1 - 1)) {
-        unit_sum(acc, partial + (size_t)b * pstride + (size_t)((k - 1) / g.zu) * g.row_blocks + rb);
-        acc = 0.0;
-      }
+      // (the next sum is a plane's barriers away)
+      if (Epi::kReduce) unit_end(g, acc, k, k0, k1, partial + (size_t)b * pstride, rb, zb);
       if (k + 1 < k1) {
         // u plane k+2 (OP_Z1: from kappa planes k+1, k+2, stored in earlier
         // steps; kappa plane k+3 takes the slot of plane k-1 below)
@@ -1683,10 +1691,7 @@ __global__ void __launch_bounds__(256, (resr_min_waves<T, V, Z1, UPD>())) k_resr
       }
       if (kk + 1 <= kt1) prep_u(kk + 2);   // kappa planes kk+1, kk+2 are in the ring
       if constexpr (UPD) {
-        if (kk < k1 && (kk % g.zu == 0 || kk == k1 - 1)) {   // the last plane of a unit
-          unit_sum(racc, upd.partial + (size_t)b * upd.pstride + (size_t)((kk - 1) / g.zu) * g.row_blocks + rb);
-          racc = 0.0;
-        }
+        if (kk < k1) unit_end(g, racc, kk, k0, k1, upd.partial + (size_t)b * upd.pstride, rb, zb);
       }
       __syncthreads();
       // in-plane full weighting of t at the owned coarse node, folded over planes
@@ -1745,7 +1750,7 @@ hipError_t zlaunch_lds(int n, int B, const T* u, const T* xc, const T* kap, cons
   constexpr int V = ZV<T>::V;
   const ZGeom g = zfine(zlds_geom<T, PRO, OP>(n, B), B, Epi::kReduce ? pstride : ~0u);
   if (!zlds_ok<T, OP, PRO>(g)) return hipErrorInvalidValue;
-  if (nparts) *nparts = g.parts();
+  if (nparts) *nparts = g.parts_code();
   const uint32_t blocks = g.blocks() * (uint32_t)B;
   const size_t lds = zlds_bytes<T, OP, PRO>(g);
   const size_t cs = PRO ? grid_stride(n / 2) : 0;
@@ -1799,7 +1804,7 @@ hipError_t zlaunch(int n, int B, const T* u, const T* kap, const int* active, do
   constexpr int V = ZV<T>::V;
   const ZGeom g = zgeom<T>(n, B);
   if (g.G < 1) return hipErrorInvalidValue;
-  if (nparts) *nparts = g.parts();
+  if (nparts) *nparts = g.parts_code();
   const uint32_t blocks = g.blocks() * (uint32_t)B;
   if (var & ZVAR_PREFETCH)
     k_zmarch<T, V, NEED_U, true, false, false, Epi><<<dim3(blocks), dim3(g.threads), 0, st>>>(
@@ -1823,7 +1828,7 @@ hipError_t zlaunch_addd(int n, int B, const T* u, const float* d, const T* kap, 
   constexpr int V = ZV<T>::V;
   const ZGeom g = zgeom<T>(n, B);
   if (g.G < 1) return hipErrorInvalidValue;
-  if (nparts) *nparts = g.parts();
+  if (nparts) *nparts = g.parts_code();
   const uint32_t blocks = g.blocks() * (uint32_t)B;
   k_zmarch<T, V, true, false, false, true, Epi><<<dim3(blocks), dim3(g.threads), 0, st>>>(
       g, grid_stride(n), T(1) / T(n), u, kap, active, partial, pstride, epi, nullptr, 0, d);
@@ -1839,7 +1844,7 @@ hipError_t zlaunch_pro(int n, int B, const T* u, const T* xc, const T* kap, cons
   constexpr int V = ZV<T>::V;
   const ZGeom g = zgeom<T>(n, B);
   if (g.G < 1) return hipErrorInvalidValue;
-  if (nparts) *nparts = g.parts();
+  if (nparts) *nparts = g.parts_code();
   const uint32_t blocks = g.blocks() * (uint32_t)B;
   k_zmarch<T, V, true, false, true, false, Epi><<<dim3(blocks), dim3(g.threads), 0, st>>>(
       g, grid_stride(n), T(1) / T(n), u, kap, active, partial, pstride, epi, xc, grid_stride(n / 2), nullptr);
@@ -2333,7 +2338,7 @@ hipError_t launch_residual_restrict_update(int n, int B, const T* kap, const T* 
   constexpr int V = ZV<T>::V;
   const ZGeom g = zfine(resr_geom<T>(n, B), B, s.pstride);
   if (!presmooth_usable<T>(n, B)) return hipErrorInvalidValue;
-  if (nparts) *nparts = g.parts();
+  if (nparts) *nparts = g.parts_code();
   ResrUpd<T> u;
   u.q = q;
   u.r1 = r1;
