@@ -4,6 +4,26 @@
 
 static std::string g_create_error;
 
+namespace {
+
+// Step-level calls return with their work queued.  A context that was given the
+// null stream solves on a stream of its own (graphs cannot be captured on the
+// null stream), but what such a call queues goes to the null stream itself:
+// the caller's memory is ordered by it, and two contexts' own streams are not
+// ordered with each other (a freed output of one could be the next output of the
+// other while the first is still being written).  The own stream is a blocking
+// one, so what the context does next waits for this work and the other way round.
+struct QueuedCall {
+  mlmc_ctx* ctx;
+  hipStream_t st;
+  explicit QueuedCall(mlmc_ctx* c) : ctx(c), st(c->st) {
+    if (c->own_stream) c->st = nullptr;
+  }
+  ~QueuedCall() { ctx->st = st; }
+};
+
+}  // namespace
+
 extern "C" {
 
 size_t mlmc_grid_stride(int32_t n) { return n >= 2 ? grid_stride(n) : 0; }
@@ -199,6 +219,7 @@ int mlmc_kl_modes(double corr_len, double sigma2, int32_t n_modes, int32_t* trip
 
 int mlmc_draw_xi(mlmc_ctx* ctx, int32_t level, uint64_t first, int64_t count, double* xi) {
   if (!ctx) return MLMC_E_INVALID;
+  const QueuedCall queued(ctx);
   if (count < 0 || (count > 0 && !xi) || level < 0) FAIL(MLMC_E_INVALID, "bad draw_xi arguments");
   LAUNCH(MLMC_K_XI, (double)count * ctx->cfg.n_modes * 8,
          launch_draw_xi(ctx->cfg.seed, level, first, count, ctx->cfg.n_modes, xi, ctx->st));
@@ -207,6 +228,7 @@ int mlmc_draw_xi(mlmc_ctx* ctx, int32_t level, uint64_t first, int64_t count, do
 
 int mlmc_field(mlmc_ctx* ctx, int32_t n, int64_t count, const double* xi, double* kappa, float* kappa32) {
   if (!ctx) return MLMC_E_INVALID;
+  const QueuedCall queued(ctx);
   if (count < 0 || count > (1 << 30) || (count > 0 && (!xi || !kappa))) FAIL(MLMC_E_INVALID, "bad field arguments");
   if (!mesh_of_config(ctx, n)) FAIL(MLMC_E_INVALID, "mesh " + std::to_string(n) + " is not a level mesh");
   if (count == 0) return MLMC_OK;
@@ -215,6 +237,7 @@ int mlmc_field(mlmc_ctx* ctx, int32_t n, int64_t count, const double* xi, double
 
 int mlmc_apply(mlmc_ctx* ctx, int32_t n, int64_t count, const double* kappa, const double* u, double* y) {
   if (!ctx) return MLMC_E_INVALID;
+  const QueuedCall queued(ctx);
   if (n < 2 || !is_pow2(n) || count < 0 || count > (1 << 30) || (count > 0 && (!kappa || !u || !y)) ||
       (count > 0 && u == y))
     FAIL(MLMC_E_INVALID, "bad apply arguments");
@@ -226,6 +249,7 @@ int mlmc_apply(mlmc_ctx* ctx, int32_t n, int64_t count, const double* kappa, con
 
 int mlmc_apply_f32(mlmc_ctx* ctx, int32_t n, int64_t count, const float* kappa, const float* u, float* y) {
   if (!ctx) return MLMC_E_INVALID;
+  const QueuedCall queued(ctx);
   if (n < 2 || !is_pow2(n) || n > 1024 || count < 0 || count > (1 << 30) || (count > 0 && (!kappa || !u || !y)) ||
       (count > 0 && u == y))
     FAIL(MLMC_E_INVALID, "bad apply arguments");
@@ -238,6 +262,7 @@ int mlmc_apply_f32(mlmc_ctx* ctx, int32_t n, int64_t count, const float* kappa, 
 int mlmc_jacobi(mlmc_ctx* ctx, int32_t n, int64_t count, const double* kappa, const double* b, double c,
                 double* z) {
   if (!ctx) return MLMC_E_INVALID;
+  const QueuedCall queued(ctx);
   if (n < 2 || !is_pow2(n) || n > 1024 || count < 0 || count > (1 << 30) || (count > 0 && (!kappa || !b || !z)) ||
       (count > 0 && b == z) || !std::isfinite(c))
     FAIL(MLMC_E_INVALID, "bad jacobi arguments");
@@ -250,6 +275,7 @@ int mlmc_jacobi(mlmc_ctx* ctx, int32_t n, int64_t count, const double* kappa, co
 
 int mlmc_vcycle(mlmc_ctx* ctx, int32_t n, int64_t count, const double* kappa, const double* r, double* z) {
   if (!ctx) return MLMC_E_INVALID;
+  const QueuedCall queued(ctx);
   if (ctx->server) FAIL(MLMC_E_INVALID, "the context is serving");
   if (n < 2 || !is_pow2(n) || count < 1 || count > (1 << 30) || !kappa || !r || !z)
     FAIL(MLMC_E_INVALID, "bad vcycle arguments");
@@ -273,6 +299,7 @@ int mlmc_vcycle(mlmc_ctx* ctx, int32_t n, int64_t count, const double* kappa, co
 
 int mlmc_vcycle_f32(mlmc_ctx* ctx, int32_t n, int64_t count, const float* kappa, const float* r, float* z) {
   if (!ctx) return MLMC_E_INVALID;
+  const QueuedCall queued(ctx);
   if (ctx->server) FAIL(MLMC_E_INVALID, "the context is serving");
   if (n < 2 || !is_pow2(n) || n > 1024 || count < 1 || count > (1 << 30) || !kappa || !r || !z)
     FAIL(MLMC_E_INVALID, "bad vcycle arguments");
@@ -316,6 +343,7 @@ int mlmc_solve(mlmc_ctx* ctx, int32_t n, int64_t count, const double* kappa, dou
 
 int mlmc_qoi(mlmc_ctx* ctx, int32_t n, int64_t count, const double* u, double* q) {
   if (!ctx) return MLMC_E_INVALID;
+  const QueuedCall queued(ctx);
   if (ctx->server) FAIL(MLMC_E_INVALID, "the context is serving");
   if (n < 2 || !is_pow2(n) || count < 1 || count > (1 << 30) || !u || !q) FAIL(MLMC_E_INVALID, "bad qoi arguments");
   if (ctx->cfg.qoi == 1 && n % 4) FAIL(MLMC_E_INVALID, "subcube QoI needs 4 | n");
@@ -329,6 +357,7 @@ extern "C" {
 
 int mlmc_qoi_noalloc(mlmc_ctx* ctx, int32_t n, int64_t count, const double* u, double* q) {
   if (!ctx) return MLMC_E_INVALID;
+  const QueuedCall queued(ctx);
   if (n < 2 || !is_pow2(n) || n > 1024 || count < 1 || count > (1 << 30) || !u || !q)
     FAIL(MLMC_E_INVALID, "bad qoi arguments");
   if (ctx->cfg.qoi == 1 && n % 4) FAIL(MLMC_E_INVALID, "subcube QoI needs 4 | n");
