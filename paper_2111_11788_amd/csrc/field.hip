@@ -426,10 +426,12 @@ void launch_field_plane_mfma(int n, int M, int K1, int64_t count, const double* 
 //     Phi_x operand is block diagonal (zero where a column belongs to another
 //     row), so a tile holds 256 elements on every mesh.
 // Bound: the 12 bytes written per element and the fp64 exponential (25 million
-// elements, 32^3 x 777, M = 256: 102 us a call, 3.0 TB/s, against 731 us with
+// elements, 32^3 x 777, M = 256: 91 us a call, 3.3 TB/s, against 731 us with
 // k_field_sep, whose sums read both operands from LDS; 13001 samples of 8^3, M =
-// 128: 207 -> 45 us; one of 16^3: 48 -> 7.5 us).  Chunks of 256 modes: 40 KB of LDS,
-// four workgroups per CU; 128 modes measured 113 us on the first of these.
+// 128: 207 -> 42 us; one of 16^3: 48 -> 6.4 us).  Chunks of 256 modes: 40 KB of LDS,
+// four workgroups per CU; 128 modes and five per CU, with spills, measured 111 us on
+// the first of these against 107.  Stores past the caches: 107 -> 91 us there, and no
+// reader of kappa measured slower (1131 pairs of 16^3 / 8^3: 982 -> 966 us a call).
 // modes of a chunk, samples of a pass, and the doubles that xi and H share
 constexpr int kRowsChunk = 256;
 __host__ __device__ constexpr int field_rows_chunk(int M) { return M < kRowsChunk ? M : kRowsChunk; }
@@ -540,8 +542,8 @@ __global__ void __launch_bounds__(256) k_field_rows(int n, int M, int K1, int64_
             const int64_t r = rowmap ? rowmap[s] : s;
             const double k = exp(acc[q]);
             const int64_t at = r * ne + (row0 + (rho & 15)) * n + ((16 * c + lc) & (n - 1));
-            kappa[at] = k;
-            if (kappa32) kappa32[at] = (float)k;
+            __builtin_nontemporal_store(k, kappa + at);
+            if (kappa32) __builtin_nontemporal_store((float)k, kappa32 + at);
           }
         }
       }
