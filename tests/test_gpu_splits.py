@@ -37,3 +37,15 @@ def test_large_meshes_sum_in_an_order_of_their_own(n, B, prec, solver, deg):
     kap = ctx.field(n, ctx.draw_xi(0, 0, B))
     _same_bits_alone(ctx, n, kap, [(0, 1), (B - 1, B), (1, 4)])
     ctx.close()
+
+
+# meshes whose default is a whole solve in one workgroup, on the level-by-level
+# kernels: split stencil launches and sums per unit of planes
+@pytest.mark.parametrize("n,B,prec,deg", [(4, 300, 1, 1), (8, 70, 0, 1), (8, 1500, 1, 2), (16, 700, 1, 1),
+                                          (16, 700, 1, 2), (16, 1300, 0, 1)])
+def test_small_meshes_on_the_level_kernels(n, B, prec, deg):
+    ctx = mm.Context(_wl(n0=n, precision=prec), cheb_degree=deg, arena_bytes=2 << 30)
+    ctx.set_tuning(fuse=ctx.tuning()["fuse"] & ~mm.FUSE_SOLVE, vsmall_fp32=0, vsmall_fp64=0)
+    kap = ctx.field(n, ctx.draw_xi(0, 0, B))
+    _same_bits_alone(ctx, n, kap, [(0, 1), (B - 1, B), (1, 4)])
+    ctx.close()
