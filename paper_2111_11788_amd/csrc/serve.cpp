@@ -5,7 +5,10 @@
 // (Sec. 2.2).  Each mesh has a resident pool of S slots carved from the
 // context's arena (the HBM budget): every slot keeps its kappa, its whole
 // fp32 multigrid hierarchy and its solver vectors on the device until the
-// solve finishes.  A host thread and a stream per pool run steps; each step
+// solve finishes.  A host thread and a stream per pool run steps.  A pool of a
+// mesh up to 16^3 solves what a step admits in that step, one workgroup per solve
+// (step_whole; it is carved like the others, of which it uses kappa, u and the
+// scalars).  In the pools of larger meshes each step
 //   admits queued jobs into free slots (draw xi, KLE field, coarse kappa,
 //   x = 0, r = b), restarts the fp32 inner PCG of slots that need it, runs one
 //   inner PCG iteration for every slot in its inner phase, applies the fp64
@@ -14,7 +17,7 @@
 // So requests join a batch that is already iterating as soon as a slot is
 // free (continuous batching), pools of different meshes run concurrently, and
 // each slot's arithmetic is exactly that of a slot solved alone: every
-// reduction is per slot with a geometry fixed by the pool size.
+// reduction is per slot, in an order of its own.
 #include "engine.hpp"
 
 #include <atomic>
@@ -200,11 +203,12 @@ int step_whole(Pool& p, int c) {
   SRV_LAUNCH(launch_field(n, ctx->cfg.n_modes, c, p.xi, ctx->d_sqrtlam, ctx->d_triples, tab, ctx->K1, p.kap64,
                           nullptr, st, p.d_slots, ctx->cfg.precision == MLMC_PREC_MIXED_BF16KLE,
                           field_separable(ctx, c) ? ctx->d_xperm : nullptr, ctx->d_xoff));
-  // as many iterations as the steps after which a slot is given up (pool_loop)
-  const int cap = ctx->cfg.max_iter > (1 << 28) ? 1 << 30 : 4 * ctx->cfg.max_iter;
+  // as many iterations, however many refinements they take, as the steps after
+  // which a slot is given up (pool_loop)
+  const int cap = ctx->cfg.max_iter > (1 << 28) ? 1 << 30 : 4 * ctx->cfg.max_iter + 1;
   const ChebCoeffs& ch = ctx->cheb;
   SRV_LAUNCH(launch_solve_small(n, c, ch.degree, ch.c1, ch.c2, p.kap64, nullptr, h * h * h, p.u, p.w.outer.s.active,
-                                p.w.inner.s.iters, ctx->cfg.rtol, kInnerTol, cap, kMaxOuter, st, nullptr, p.d_slots));
+                                p.w.inner.s.iters, ctx->cfg.rtol, kInnerTol, cap, cap, st, nullptr, p.d_slots));
   SolveState dn = view(p.w.outer.s, p.m_new, p.phase);
   uint32_t np = 0;
   SRV_LAUNCH(launch_qoi_partial(n, S, ctx->cfg.qoi, p.u, dn, &np, st, true));
