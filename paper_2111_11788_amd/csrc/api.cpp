@@ -467,7 +467,7 @@ int mlmc_autotune(mlmc_ctx* ctx, int32_t level, int32_t batch, mlmc_tuning* best
   const int nf = ctx->cfg.n0 << level, nc = level > 0 ? nf / 2 : 0;
   for (int f : {MLMC_FUSE_PROLONG, MLMC_FUSE_UPDATE, MLMC_FUSE_REFINE, MLMC_FUSE_RESTRICT, MLMC_FUSE_PRESMOOTH,
                 MLMC_FUSE_DIRECTION, MLMC_FUSE_RUPDATE, MLMC_FUSE_SOLVE, MLMC_FUSE_PACK}) {
-    if (f == MLMC_FUSE_SOLVE && nf > 8 && !(nc >= 4 && nc <= 8)) continue;   // no 4^3 or 8^3 solve here
+    if (f == MLMC_FUSE_SOLVE && nf > 16 && !(nc >= 4 && nc <= 16)) continue;   // no 4^3 to 16^3 solve here
     if (f == MLMC_FUSE_PACK) continue;   // a single level has nothing to pack
     mlmc_tuning c = best; c.fuse ^= f;
     if (int rc = trial(c)) return rc;
