@@ -170,8 +170,6 @@ hipError_t launch_fill_interior(int n, int B, T* v, double value, const int* act
 // one kernel, one workgroup per sample, all coarse data in LDS.
 // kap_levels[l] is the kappa of mesh n0 >> l; b, x are grid-layout n0 vectors.
 template <class T>
-size_t vsmall_lds_bytes(int n0);
-template <class T>
 hipError_t launch_vsmall(int n0, int B, int degree, const double* c1, const double* c2,
                          const T* const* kap_levels, const T* b, T* x, const int* active,
                          hipStream_t st);

@@ -1056,7 +1056,8 @@ __global__ void __launch_bounds__(HALO == HALO_LDS ? 512 : 256) k_zlds(ZGeom g, 
   const int gx = tid & (G - 1), jr = tid >> gsh;
   const int j = j0 + jr, i0 = gx * V;
   const bool valid = jr < R && j <= n - 1 && k0 < k1;
-  // a row fits in one wave (zlds_ok): halos by DPP, no branch in the gather
+  // a row fits in one wave (zlds_ok): halos by DPP, no branch in the gather; a
+  // row of two waves (HALO_LDS) reads them from LDS
   const T* ub = (NEED_U && u) ? u + (size_t)b * stride : nullptr;
   if (NEED_U && op.ustate && (op.ustate[b] & 8)) ub = op.u1 + (size_t)b * stride;
   const float* db = ADDD ? op.d + (size_t)b * stride : nullptr;

@@ -1039,9 +1039,6 @@ SmallArgs small_args(int n0, int degree, const double* c1, const double* c2) {
 }  // namespace
 
 template <class T>
-size_t vsmall_lds_bytes(int n0) { return levels_bytes<T>(n0); }
-
-template <class T>
 hipError_t launch_vsmall(int n0, int B, int degree, const double* c1, const double* c2, const T* const* kap_levels,
                          const T* b, T* x, const int* active, hipStream_t st) {
   if (degree < 1 || degree > 16) return hipErrorInvalidValue;
@@ -1115,8 +1112,6 @@ hipError_t launch_solve_small64(int n, int B, bool gmg, int degree, const double
   return hipGetLastError();
 }
 
-template size_t vsmall_lds_bytes<float>(int);
-template size_t vsmall_lds_bytes<double>(int);
 template hipError_t launch_vsmall<float>(int, int, int, const double*, const double*, const float* const*,
                                          const float*, float*, const int*, hipStream_t);
 template hipError_t launch_vsmall<double>(int, int, int, const double*, const double*, const double* const*,
