@@ -60,8 +60,10 @@ inline void zsplit(ZGeom& g, long waves) {
     // cheap while the chip is not full (32 pairs of 32^3 / 16^3, mixed: 1.92 ->
     // 1.31 ms with chunks of 4 planes in place of 16; a 64^3 level of three
     // 128^3 samples likewise).  A launch of one to one and a half times the
-    // chip's waves (the 14-row tiles of 256 samples of 64^3) is split once: half
-    // of its second round would be idle (268 -> 231 us)
+    // chip's waves is split once: half of its second round would be idle (the
+    // 14-row tiles of 256 samples of 64^3: 268 -> 231 us; solves of 300 and 370
+    // samples of 64^3 7 to 9% faster, of 1200 of 32^3 10%, fp64 of 140 of 64^3 8% and
+    // of 600 of 32^3 2%, but of 760 2% slower)
     g.zu = n == 64 ? 8 : 4;
     g.zlen = (n - 1 + g.zu - 1) / g.zu * g.zu;
     g.zc = 1;
