@@ -127,6 +127,7 @@ void mlmc_destroy(mlmc_ctx* ctx) {
   mlmc_serve_stop(ctx);
   // teardown: errors have nowhere to go
   (void)hipStreamSynchronize(ctx->st);
+  if (ctx->own_stream) (void)hipStreamSynchronize(nullptr);   // queued calls (QueuedCall)
   for (auto& r : ctx->prof) {
     (void)hipEventDestroy(r.a);
     (void)hipEventDestroy(r.b);

@@ -62,3 +62,17 @@ def test_queued_calls_and_solves_of_one_context_are_ordered():
         for g, w in zip(steps(lambda: None), want):
             assert torch.equal(g, w)
     ctx.close()
+
+
+def test_closing_a_context_waits_for_its_queued_calls():
+    n, count = 32, 400
+    wl = Workload("streams", n0=n, levels=1, sigma2=1.0, corr_len=0.3, n_modes=64, qoi=0, rtol=1e-8, max_iter=100,
+                  solver=0, precision=1, batch=8)
+    ctx = mm.Context(wl, arena_bytes=64 << 20)
+    xi = ctx.draw_xi(0, 0, count)
+    want = ctx.field(n, xi)
+    torch.cuda.synchronize()
+    k = [ctx.field(n, xi) for _ in range(30)]
+    ctx.close()
+    assert torch.cuda.current_stream().query()   # nothing left running
+    assert all(torch.equal(v, want) for v in (k[0], k[-1]))
