@@ -22,6 +22,12 @@ struct QueuedCall {
   ~QueuedCall() { ctx->st = st; }
 };
 
+// All of the context's work, queued calls included
+hipError_t wait_for(mlmc_ctx* ctx) {
+  const hipError_t e = hipStreamSynchronize(ctx->st);
+  return e == hipSuccess && ctx->own_stream ? hipStreamSynchronize(nullptr) : e;
+}
+
 }  // namespace
 
 extern "C" {
@@ -126,8 +132,7 @@ void mlmc_destroy(mlmc_ctx* ctx) {
   if (!ctx) return;
   mlmc_serve_stop(ctx);
   // teardown: errors have nowhere to go
-  (void)hipStreamSynchronize(ctx->st);
-  if (ctx->own_stream) (void)hipStreamSynchronize(nullptr);   // queued calls (QueuedCall)
+  (void)wait_for(ctx);
   for (auto& r : ctx->prof) {
     (void)hipEventDestroy(r.a);
     (void)hipEventDestroy(r.b);
@@ -751,7 +756,7 @@ int mlmc_last_plan(const mlmc_ctx* ctx, mlmc_plan_task* out, int32_t max, int32_
 
 int mlmc_set_profiling(mlmc_ctx* ctx, int32_t on) {
   if (!ctx) return MLMC_E_INVALID;
-  HIPCHK(hipStreamSynchronize(ctx->st));
+  HIPCHK(wait_for(ctx));
   for (auto& r : ctx->prof) {
     ctx->event_pool.push_back(r.a);
     ctx->event_pool.push_back(r.b);
@@ -768,7 +773,7 @@ int mlmc_set_profiling(mlmc_ctx* ctx, int32_t on) {
 int mlmc_kernel_time(mlmc_ctx* ctx, int32_t kernel_id, int32_t precision, int64_t* launches, double* total_ms,
                      double* bytes) {
   if (!ctx || kernel_id < 0 || kernel_id >= MLMC_K_COUNT || precision < 0 || precision > 1) return MLMC_E_INVALID;
-  HIPCHK(hipStreamSynchronize(ctx->st));
+  HIPCHK(wait_for(ctx));
   std::vector<int> cnt(ctx->prof_used);
   if (ctx->prof_used)
     HIPCHK(hipMemcpy(cnt.data(), ctx->prof_counts, cnt.size() * sizeof(int), hipMemcpyDeviceToHost));

@@ -76,3 +76,17 @@ def test_closing_a_context_waits_for_its_queued_calls():
     ctx.close()
     assert torch.cuda.current_stream().query()   # nothing left running
     assert all(torch.equal(v, want) for v in (k[0], k[-1]))
+
+
+def test_kernel_times_of_queued_calls():
+    n, count = 32, 400
+    wl = Workload("streams", n0=n, levels=1, sigma2=1.0, corr_len=0.3, n_modes=64, qoi=0, rtol=1e-8, max_iter=100,
+                  solver=0, precision=1, batch=8)
+    ctx = mm.Context(wl, arena_bytes=64 << 20)
+    xi = ctx.draw_xi(0, 0, count)
+    ctx.set_profiling(True)
+    k = [ctx.field(n, xi) for _ in range(20)]
+    launches, ms, nbytes = ctx.kernel_time("FIELD")[:3]
+    assert launches == 20 and ms > 0.0
+    ctx.close()
+    del k
