@@ -41,13 +41,13 @@ HBM_PEAK_GBS = 8000.0   # MI355X HBM3E, GB/s
 TRAFFIC = {
     "profile": "profiles/batched-64cube-1024_hbm_traffic.txt",
     "tuning": {"zvar_fp32": 2, "zvar_fp64": 2, "vsmall_fp32": 16, "vsmall_fp64": 8, "cheb_degree": 1, "max_batch": 256, "graph_batch": 1, "fuse": 447, "lanes": 4},
-    "sha256_16": {"common.hpp": "84103274fa2b6280", "grid.hpp": "b240c0e6cdf9fd1c", "kernels.hpp": "037887b66ba1ce4b", "krylov.hip": "cdf3168b8678bec1", "stencil.hip": "e58c30d0c1b92bf7"},
+    "sha256_16": {"common.hpp": "84103274fa2b6280", "grid.hpp": "e3f78599d0dff03e", "kernels.hpp": "e18d237468d4e408", "krylov.hip": "1ea16497f9ec62df", "stencil.hip": "ae9a65402199f55c"},
     "bytes_per_launch": {
-        "PCG_APPLY (f32)": 1654327456,
-        "CHEB_PROLONG (f32)": 522266031,
-        "RESIDUAL_RESTRICT (f32)": 395964223,
-        "PCG_UPDATE (f32)": 792139355,
-        "TRUE_RESIDUAL (f64)": 2168757237,
+        "PCG_APPLY (f32)": 1643377358,
+        "CHEB_PROLONG (f32)": 534314854,
+        "RESIDUAL_RESTRICT (f32)": 400396789,
+        "PCG_UPDATE (f32)": 792137209,
+        "TRUE_RESIDUAL (f64)": 2165908067,
     },
 }
 
@@ -56,7 +56,7 @@ TRAFFIC = {
 # (None: the whole value); the coarse V-cycle and the smoothing degree set the
 # iteration (and so launch) counts, the LDS-engine bit of zvar selects the
 # apply's engine, the DIRECTION and REFINE fusion bits its form.  Fusion bit 128 (the
-# whole solve of 4^3 / 8^3 meshes) never acts on the 64^3 workload.
+# whole solve of meshes up to 16^3) never acts on the 64^3 workload.
 FUSE_64 = 127
 TRAFFIC_TUNING_KEYS = {
     "PCG_UPDATE (f32)": {"max_batch": None, "vsmall_fp32": None, "cheb_degree": None, "fuse": FUSE_64},
