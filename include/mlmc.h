@@ -20,7 +20,8 @@
  *     owned device allocations, "host" pointers are caller-owned host memory.
  *   Stream: all device work of a context is issued on mlmc_config.stream
  *     (a hipStream_t; NULL = the null stream).  Step-level calls return once
- *     work is queued; whole-path calls (sample_level, estimate) synchronise.
+ *     work is queued; solves and whole-path calls (sample_level, estimate)
+ *     synchronise, and may use streams of their own that are ordered with it.
  *   Threading: a context is used by one host thread at a time.
  *
  * Layouts
